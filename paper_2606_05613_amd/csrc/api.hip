@@ -117,7 +117,6 @@ struct Carved {
   float *weights;
   double *partials;
   int64_t *group_start;
-  double *groups;
   uint32_t *sync;
 };
 
@@ -128,7 +127,7 @@ Carved carve(void *ws, const Layout &L) {
                 reinterpret_cast<double *>(base + L.gram), reinterpret_cast<float *>(base + L.weights),
                 reinterpret_cast<double *>(base + L.partials),
                 reinterpret_cast<int64_t *>(base + L.group_start),
-                reinterpret_cast<double *>(base + L.groups), reinterpret_cast<uint32_t *>(base + L.sync)};
+                reinterpret_cast<uint32_t *>(base + L.sync)};
 }
 
 // The cooperative kernel's grid (Grid: hybrid_grid) on the current device,
@@ -426,7 +425,8 @@ bkmoo_status bkmoo_gram(int32_t K, const void *const *grads, bkmoo_dtype dt, int
   if (e != hipSuccess) return BKMOO_EHIP;
   const StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, w.group_start, w.err,
                      shift, vec, g_grid_override.load()};
-  return hip_status(launch_gram(a, w.partials, w.groups, L.cap_groups, gram, stream));
+  if (launch_gram_partials(a, w.partials, stream) != hipSuccess) return BKMOO_EHIP;
+  return hip_status(launch_gram_finalize(a, w.partials, gram, stream));
 }
 
 bkmoo_status bkmoo_solve(int32_t K, int32_t B, const double *gram, bkmoo_method method,
@@ -456,7 +456,7 @@ bkmoo_status bkmoo_combine(int32_t K, const void *const *grads, bkmoo_dtype dt, 
   const Layout L = layout(K, N, B, dt);
   if (ws_bytes < L.total) return BKMOO_EWORKSPACE;
   const Carved w = carve(workspace, L);
-  hipError_t e = launch_schedule(bucket_offsets, B, N, combine_chunk_elems(K, dt), w.chunk_start,
+  hipError_t e = launch_schedule(bucket_offsets, B, N, gram_chunk_elems(K, dt), w.chunk_start,
                                  nullptr, w.err, nullptr, 0, stream);
   if (e != hipSuccess) return BKMOO_EHIP;
   const StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, nullptr, w.err, shift,
@@ -542,14 +542,13 @@ bkmoo_status resolve_impl(int32_t K, const void *const *grads, bkmoo_dtype dt, i
   if (e != hipSuccess) return BKMOO_EHIP;
   StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, w.group_start, w.err, shift,
                vec_in, g_grid_override.load()};
-  if ((e = launch_gram(a, w.partials, w.groups, L.cap_groups, G, stream)) != hipSuccess)
-    return BKMOO_EHIP;
-  if ((e = launch_solve(K, B, G, (int)method, iters, c, order, W, aux, stream)) != hipSuccess)
-    return BKMOO_EHIP;
-  // the combine pass cuts its own chunks (the schedule keeps the error word
-  // the Gram pass's schedule set: offsets are the same)
-  e = launch_schedule(bucket_offsets, B, N, combine_chunk_elems(K, dt), w.chunk_start, nullptr, w.err,
-                      nullptr, 0, stream);
+  if (launch_gram_partials(a, w.partials, stream) != hipSuccess) return BKMOO_EHIP;
+  if (is_exact(method)) {
+    if (launch_gram_finalize(a, w.partials, G, stream) != hipSuccess) return BKMOO_EHIP;
+    e = launch_solve(K, B, G, (int)method, iters, c, order, W, aux, stream);
+  } else {
+    e = launch_gram_solve(a, w.partials, G, (int)method, iters, c, order, W, aux, stream);
+  }
   if (e != hipSuccess) return BKMOO_EHIP;
   a.vec = vec_out;
   return hip_status(launch_combine(a, W, out, (int)out_dt, stream));

@@ -3,8 +3,9 @@
 // d = [d_(1), ..., d_(K)]).
 //
 // Bandwidth-bound: K*N*s bytes read, N*s_out written, 2K flops per
-// element.  Same chunks and 128-bit non-temporal loads as the Gram pass;
-// the K weights of a chunk's bucket are wave-uniform scalars.  Unlike the
+// element.  128-bit non-temporal loads as in the Gram pass, whose chunks are
+// cut in kCombineParts (the schedule is the Gram pass's: a schedule kernel of
+// its own cost every two-pass call 5-6 us); the K weights of a chunk's bucket are wave-uniform scalars.  Unlike the
 // Gram pass, chunks are dealt round-robin (chunk c to workgroup c mod grid),
 // so the whole grid sweeps the vector together: measured 1-2.5% faster
 // than one contiguous run per workgroup on every workload shape here, in
@@ -35,13 +36,14 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(
   constexpr int64_t C = combine_chunk_elems(K, DT);
   constexpr int EB = elem_bytes(DT);
 
-  const int64_t total = cs[B];
+  const int64_t total = cs[B] * kCombineParts;
   const int tid = threadIdx.x;
 
   for (int64_t c = blockIdx.x; c < total; c += gridDim.x) {
-    const int b = find_bucket(cs, B, c);
-    const int64_t lo = offs[b] + (c - cs[b]) * C;
+    const int b = find_bucket(cs, B, c / kCombineParts);
+    const int64_t lo = offs[b] + (c - cs[b] * kCombineParts) * C;
     const int64_t hi = lo + C < offs[b + 1] ? lo + C : offs[b + 1];
+    if (lo >= hi) continue;  // the bucket ends in an earlier part of its last Gram chunk
     float w[K];
 #pragma unroll
     for (int i = 0; i < K; ++i) w[i] = weights[(int64_t)b * K + i];

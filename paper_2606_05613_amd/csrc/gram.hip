@@ -12,11 +12,13 @@
 // non-temporal loads per iteration and accumulates all K(K+1)/2 products
 // in fp32 registers over the chunk's iterations.  Lane sums are combined by
 // a fixed xor butterfly across the wavefront, then in fp64 across the 4
-// wavefronts through LDS in wave order, and land in a per-chunk slot.  Two
-// finalize kernels add a bucket's chunk slots in fp64 in an order fixed by
-// the bucket's chunk count (groups of consecutive chunks, then the groups in
-// order).  No atomics: the result is bitwise independent of the grid and of
-// scheduling.
+// wavefronts through LDS in wave order, and land in a per-chunk slot.  The
+// finalize adds a bucket's chunk slots in fp64 in an order fixed by the
+// bucket's chunk count and N (where a bucket can have many chunks, groups of
+// consecutive chunks first, then the groups); a resolve call adds them in
+// the kernel that also solves the bucket's problem (solve.hip).  No atomics:
+// the result is bitwise independent of the grid and of scheduling.
+#include "gram_sum.h"
 #include "stream_common.h"
 
 namespace bkmoo {
@@ -120,53 +122,41 @@ __global__ __launch_bounds__(kThreads) void gram_partial_kernel(
   }
 }
 
-// Finalize, level 1: one workgroup per group of up to kFinalizeGroup
-// consecutive chunks of one bucket (grid-stride over the groups).  Wavefront
-// w handles the pairs p = w, w + 4, ...; lane l adds the group's chunks l,
-// l + 64, l + 128, ... in that order in fp64, then a fixed xor butterfly adds
-// the 64 lane sums.  The order depends only on the group's chunk count.
-__global__ __launch_bounds__(kThreads) void gram_group_kernel(
-    int K, int B, const int64_t *__restrict__ cs, const int64_t *__restrict__ gs,
-    const double *__restrict__ partials, double *__restrict__ groups) {
-  const int P = K * (K + 1) / 2;
+// Finalize, level 1 (only where a bucket can have many chunks): one workgroup
+// per group of up to kFinalizeGroup consecutive chunks of one bucket
+// (grid-stride over the groups) leaves the group's sum in the slot of the
+// group's first chunk, which only this workgroup reads.
+__global__ __launch_bounds__(kSumThreads) void gram_group_kernel(int P, int B, const int64_t *__restrict__ cs,
+                                                                 const int64_t *__restrict__ gs, double *partials) {
+  __shared__ double red[kSumThreads];
   const int64_t total = gs[B];
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   for (int64_t v = blockIdx.x; v < total; v += gridDim.x) {
     const int b = find_bucket(gs, B, v);
-    const int64_t c_lo = cs[b] + (v - gs[b]) * kFinalizeGroup;
-    const int64_t c_end = c_lo + kFinalizeGroup < cs[b + 1] ? c_lo + kFinalizeGroup : cs[b + 1];
-    for (int p = wave; p < P; p += kThreads / kWave) {
-      double s = 0.0;
-      for (int64_t c = c_lo + lane; c < c_end; c += kWave) s += partials[c * P + p];
-#pragma unroll
-      for (int off = kWave / 2; off >= 1; off >>= 1) s += __shfl_xor(s, off, kWave);
-      if (lane == 0) groups[v * P + p] = s;
-    }
+    const int64_t c0 = cs[b] + (v - gs[b]) * kFinalizeGroup, left = cs[b + 1] - c0;
+    const double s = sum_slots<kSumThreads>(partials, c0, left < kFinalizeGroup ? left : kFinalizeGroup, 1, P, red);
+    if ((int)threadIdx.x < P) partials[c0 * P + threadIdx.x] = s;
+    __syncthreads();  // `red` before the next group
   }
 }
 
-// Finalize, level 2: one wavefront per bucket adds the bucket's group sums in
-// group order and writes the symmetric K x K matrix (NaN everywhere when the
-// offsets were rejected by the schedule).
-__global__ __launch_bounds__(kWave) void gram_finalize_kernel(
-    int K, const int64_t *__restrict__ gs, const double *__restrict__ groups,
-    const uint32_t *__restrict__ err, double *__restrict__ gram) {
-  const int b = blockIdx.x;
+// Finalize, level 2: one workgroup per bucket adds the bucket's chunk slots
+// (step 1) or group sums (step kFinalizeGroup) and writes the symmetric
+// K x K matrix (NaN everywhere when the offsets were rejected by the
+// schedule).
+__global__ __launch_bounds__(kSumThreads) void gram_finalize_kernel(int K, const int64_t *__restrict__ cs, int step,
+                                                                    const double *__restrict__ partials,
+                                                                    const uint32_t *__restrict__ err,
+                                                                    double *__restrict__ gram) {
+  __shared__ double red[kSumThreads];
+  const int64_t b = blockIdx.x;
   const int P = K * (K + 1) / 2;
-  const bool bad = (*err & kErrOffsets) != 0u;
-  const int64_t g0 = gs[b], g1 = gs[b + 1];
-  for (int p = threadIdx.x; p < P; p += kWave) {
-    double s = 0.0;
-    for (int64_t g = g0; g < g1; ++g) s += groups[g * P + p];
-    if (bad) s = __builtin_nan("");
-    int i = 0, rem = p;
-    while (rem >= K - i) {
-      rem -= K - i;
-      ++i;
-    }
-    const int j = i + rem;
-    gram[((int64_t)b * K + i) * K + j] = s;
-    gram[((int64_t)b * K + j) * K + i] = s;
+  double s = sum_slots<kSumThreads>(partials, cs[b], (cs[b + 1] - cs[b] + step - 1) / step, step, P, red);
+  if ((int)threadIdx.x < P) {
+    if (*err & kErrOffsets) s = __builtin_nan("");
+    int i, j;
+    pair_of((int)threadIdx.x, K, i, j);
+    gram[(b * K + i) * K + j] = s;
+    gram[(b * K + j) * K + i] = s;
   }
 }
 
@@ -210,17 +200,21 @@ hipError_t dispatch_gram(const StreamArgs &a, double *partials, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_gram(const StreamArgs &a, double *partials, double *groups, int64_t cap_groups,
-                       double *gram, hipStream_t s) {
+int gram_sum_step(int K, int dt, int64_t N) { return N / gram_chunk_elems(K, dt) < kSumDirect ? 1 : kFinalizeGroup; }
+
+hipError_t launch_gram_partials(const StreamArgs &a, double *partials, hipStream_t s) {
   hipError_t e = a.dt == F32 ? dispatch_gram<F32>(a, partials, s) : dispatch_gram<BF16>(a, partials, s);
-  if (e != hipSuccess) return e;
-  const int64_t limit = (int64_t)device_cu_count() * 8;
-  const int64_t ggrid = cap_groups < limit ? cap_groups : limit;
-  hipLaunchKernelGGL(gram_group_kernel, dim3((unsigned)(ggrid > 0 ? ggrid : 1)), dim3(kThreads), 0, s,
-                     a.K, a.B, a.chunk_start, a.group_start, partials, groups);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(gram_finalize_kernel, dim3((unsigned)a.B), dim3(kWave), 0, s, a.K,
-                     a.group_start, groups, a.err, gram);
+  if (e != hipSuccess || gram_sum_step(a.K, a.dt, a.N) == 1) return e;
+  const int64_t groups = a.N / (gram_chunk_elems(a.K, a.dt) * kFinalizeGroup) + a.B;
+  const int64_t limit = (int64_t)device_cu_count() * 4;
+  hipLaunchKernelGGL(gram_group_kernel, dim3((unsigned)(groups < limit ? groups : limit)), dim3(kSumThreads), 0, s,
+                     pairs(a.K), a.B, a.chunk_start, a.group_start, partials);
+  return hipGetLastError();
+}
+
+hipError_t launch_gram_finalize(const StreamArgs &a, const double *partials, double *gram, hipStream_t s) {
+  hipLaunchKernelGGL(gram_finalize_kernel, dim3((unsigned)a.B), dim3(kSumThreads), 0, s, a.K, a.chunk_start,
+                     gram_sum_step(a.K, a.dt, a.N), partials, a.err, gram);
   return hipGetLastError();
 }
 

@@ -1,0 +1,66 @@
+// The Gram finalize's sum of one bucket's partial slots, shared by the
+// kernel that only writes the matrix and the one that solves it as well.
+#pragma once
+
+#include "internal.h"
+
+namespace bkmoo {
+
+namespace {
+
+// Workgroup of the kernels that add up a bucket's slots: at K = 16 (136
+// pairs) three rows of threads still read slots side by side.
+constexpr int kSumThreads = 512;
+static_assert(kSumThreads >= pairs(kMaxK), "a thread per pair");
+
+// Partial loads a thread keeps in flight.  The sums wait for memory, not for
+// bandwidth: with the loads one behind the other a group of 1024 slots of
+// the K = 8 Gram took 40 us, the same slots in groups of 64 and batches of 16
+// take 4 us.
+constexpr int kSumBatch = 16;
+
+// Sum over i = 0..n-1 of the P entries of slot c0 + i * step, for a whole
+// workgroup of T threads: thread t adds pair t % P of the slots t / P,
+// t / P + T / P, ... ascending, then the T / P rows are added ascending.  The
+// order depends on n, P and T alone.  Thread p < P returns pair p's sum;
+// `red` holds T doubles of LDS (it may be reused after the next barrier).
+template <int T>
+__device__ __forceinline__ double sum_slots(const double *__restrict__ slots, int64_t c0, int64_t n, int64_t step,
+                                            int P, double *red) {
+  const int t = threadIdx.x, rows = T / P, r = t / P, p = t - r * P;
+  double s = 0.0;
+  if (r < rows) {
+    const double *base = slots + c0 * P + p;
+    for (int64_t i = r; i < n; i += (int64_t)rows * kSumBatch) {
+      double x[kSumBatch];
+#pragma unroll
+      for (int u = 0; u < kSumBatch; ++u) {
+        const int64_t j = i + (int64_t)u * rows;
+        x[u] = j < n ? base[j * step * P] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < kSumBatch; ++u) s += x[u];
+    }
+    red[t] = s;
+  }
+  __syncthreads();
+  if (t < P) {
+    s = red[t];
+    for (int q = 1; q < rows; ++q) s += red[q * P + t];
+  }
+  return s;
+}
+
+// Task pair (i <= j) of entry p of the row-major upper triangle.
+__device__ __forceinline__ void pair_of(int p, int K, int &i, int &j) {
+  i = 0;
+  while (p >= K - i) {
+    p -= K - i;
+    ++i;
+  }
+  j = i + p;
+}
+
+}  // namespace
+
+}  // namespace bkmoo

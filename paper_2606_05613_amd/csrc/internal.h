@@ -44,13 +44,29 @@ constexpr int64_t shape_elems(PassShape p, int dt) {
 }
 constexpr int64_t gram_chunk_elems(int K, int dt) { return shape_elems(gram_shape(K), dt); }
 constexpr int64_t combine_chunk_elems(int K, int dt) { return shape_elems(combine_shape(K), dt); }
+// The combine pass cuts every Gram chunk into this many of its own, so that
+// one schedule serves both passes.
+constexpr int kCombineParts = 2;
+constexpr bool combine_parts_fit() {
+  for (int K = kMinK; K <= kMaxK; ++K)
+    for (int dt = 0; dt < 2; ++dt)
+      if (gram_chunk_elems(K, dt) != kCombineParts * combine_chunk_elems(K, dt)) return false;
+  return true;
+}
+static_assert(combine_parts_fit(), "a Gram chunk is kCombineParts combine chunks");
 
 constexpr int pairs(int K) { return K * (K + 1) / 2; }
 
-// The Gram finalize adds a bucket's chunk slots in groups of this many
-// consecutive chunks (one workgroup per group), then the group sums in group
-// order: the summation order depends only on the bucket's chunk count.
-constexpr int kFinalizeGroup = 1024;
+// The Gram finalize adds a bucket's chunk slots directly, one workgroup per
+// bucket, where no bucket can have kSumDirect chunks; beyond that groups of
+// this many consecutive chunks come first (one workgroup per group, so that a
+// single large bucket is not added by one), then the group sums.  Groups of
+// 64 fill the chip sooner than the 1024 used before: K=8 bf16, one bucket of
+// 124M elements (3,798 chunks), 40 + 5 us for the two kernels with 1024.
+constexpr int kFinalizeGroup = 64;
+constexpr int64_t kSumDirect = 512;
+// Size of a finalize group in the workspace's layout (see Layout::reserve).
+constexpr int kLayoutGroup = 1024;
 
 // Partial-Gram slots the workspace always has room for (the pipelined
 // cooperative kernel uses two sets of one slot per workgroup that holds data).
@@ -74,12 +90,14 @@ constexpr int kFlagCopies = 8;
 //   partials            fp64  [cap][P]    cap = ceil(N / C) + B (at least kCoopSlots slots of P
 //                                         rounded up to even)
 //   group_start         int64 [B + 1]     (prefix sum of finalize groups per bucket)
-//   groups              fp64  [gcap][P]   gcap = cap / kFinalizeGroup + B + 1
+//   reserve             fp64  [cap / kLayoutGroup + B + 1][P]  unused (the group sums lie in
+//                       the partial slots); it keeps a workspace's size, and with it which calls
+//                       the library's fixed scratch can hold, as callers know them
 //   sync                uint32 [1 + kFlagCopies][B][kSyncStride]  cooperative path: arrival
 //                       counters, then kFlagCopies copies of the flags
 struct Layout {
-  size_t err, chunk_start, gram, weights, partials, group_start, groups, sync, total;
-  int64_t cap_chunks, cap_groups;
+  size_t err, chunk_start, gram, weights, partials, group_start, reserve, sync, total;
+  int64_t cap_chunks;
 };
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -99,9 +117,8 @@ inline Layout layout(int K, int64_t N, int B, int dt) {
   const int64_t part = L.cap_chunks * pairs(K) > kCoopSlots * (pairs(K) + (pairs(K) & 1))
                            ? L.cap_chunks * pairs(K) : kCoopSlots * (pairs(K) + (pairs(K) & 1));
   L.partials = o;       o = align256(o + sizeof(double) * (size_t)part);
-  L.cap_groups = L.cap_chunks / kFinalizeGroup + B + 1;
   L.group_start = o;    o = align256(o + sizeof(int64_t) * (size_t)(B + 1));
-  L.groups = o;         o = align256(o + sizeof(double) * (size_t)L.cap_groups * pairs(K));
+  L.reserve = o;        o = align256(o + sizeof(double) * (size_t)(L.cap_chunks / kLayoutGroup + B + 1) * pairs(K));
   L.sync = o;           o = align256(o + sizeof(uint32_t) * (1 + kFlagCopies) * (size_t)B * kSyncStride);
   L.total = o;
   return L;
@@ -139,10 +156,15 @@ struct StreamArgs {
 hipError_t launch_schedule(const int64_t *offsets, int B, int64_t N, int64_t C, int64_t *chunk_start,
                            int64_t *group_start, uint32_t *err, uint32_t *sync, int64_t nsync,
                            hipStream_t s);
-// Gram pass: per-chunk partials, group sums, then the per-bucket matrices.
-// `cap_groups` bounds the number of finalize groups (sizes the group grid).
-hipError_t launch_gram(const StreamArgs &a, double *partials, double *groups, int64_t cap_groups,
-                       double *gram, hipStream_t s);
+// Gram pass: per-chunk partials (and group sums, left in the slots of the
+// groups' first chunks), then the per-bucket matrices.  gram_sum_step is the
+// distance of the slots that the finalize adds up (1: the chunks).
+int gram_sum_step(int K, int dt, int64_t N);
+hipError_t launch_gram_partials(const StreamArgs &a, double *partials, hipStream_t s);
+hipError_t launch_gram_finalize(const StreamArgs &a, const double *partials, double *gram, hipStream_t s);
+// The finalize and the solve (not the exact methods) in one kernel.
+hipError_t launch_gram_solve(const StreamArgs &a, const double *partials, double *gram, int method, int max_iter,
+                             double c, const int8_t *order, float *weights, double *aux, hipStream_t s);
 hipError_t launch_solve(int K, int B, const double *gram, int method, int max_iter, double c,
                         const int8_t *order, float *weights, double *aux, hipStream_t s);
 hipError_t launch_combine(const StreamArgs &a, const float *weights, void *out, int out_dt,

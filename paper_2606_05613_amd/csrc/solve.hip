@@ -4,6 +4,7 @@
 // solvers are in solve_impl.h).  This file is compiled without
 // floating-point contraction so every scalar expression rounds exactly as
 // written.
+#include "gram_sum.h"
 #include "solve_impl.h"
 
 namespace bkmoo {
@@ -55,6 +56,65 @@ __global__ __launch_bounds__(kWave) void lane_solve_kernel(const double *__restr
   }
 }
 
+// A resolve call's finalize and solve in one launch, a workgroup per bucket:
+// the workgroup adds the bucket's partial slots (in the order of the Gram
+// finalize, so the matrix is bit for bit what bkmoo_gram writes) into LDS,
+// its first wavefront solves from there.  As two kernels with a launch each
+// the smallest step spent 13 of its 41 us here.  KT = 0: K at run time, the
+// sequential solvers (K > 10).
+template <int KT>
+__global__ __launch_bounds__(kSumThreads) void gram_solve_kernel(int Krt, const int64_t *__restrict__ cs, int step,
+                                                                 const double *__restrict__ partials,
+                                                                 const uint32_t *__restrict__ err, int method,
+                                                                 int iters, double c,
+                                                                 const int8_t *__restrict__ order,
+                                                                 double *__restrict__ gram,
+                                                                 float *__restrict__ weights,
+                                                                 double *__restrict__ aux) {
+  __shared__ Shared S;
+  __shared__ double red[kSumThreads];
+  const int K = KT > 0 ? KT : Krt, P = K * (K + 1) / 2;
+  const int64_t b = blockIdx.x;
+  const int t = threadIdx.x;
+  if (t == 0) S.bad = 0;
+  double s = sum_slots<kSumThreads>(partials, cs[b], (cs[b + 1] - cs[b] + step - 1) / step, step, P, red);
+  if (t < P) {
+    if (*err & kErrOffsets) s = __builtin_nan("");
+    int i, j;
+    pair_of(t, K, i, j);
+    S.G[i * K + j] = s;
+    S.G[j * K + i] = s;
+    if (!__builtin_isfinite(s)) S.bad = 1;
+  }
+  __syncthreads();
+  if (t >= kWave) {  // the other wavefronts write the matrix
+    for (int e = t - kWave; e < K * K; e += kSumThreads - kWave) gram[b * K * K + e] = S.G[e];
+    return;
+  }
+  double wt = 0.0, ax = 0.0;
+  if constexpr (KT == 0) {
+    solver_run<WaveSync>(S, K, method, iters, c, order, b, t, &wt, &ax);
+  } else {
+    if (S.bad || (method != MGDA && method != CAGRAD))
+      solver_run<WaveSync>(S, K, method, iters, c, order, b, t, &wt, &ax);
+    else if (method == MGDA)
+      wt = ax = lane_solve_mgda<KT>(S.G, iters, t);
+    else
+      lane_solve_cagrad<KT>(S.G, iters, c, t, &wt, &ax);
+  }
+  if (t < K) {
+    weights[b * K + t] = (float)wt;
+    if (aux) aux[b * K + t] = ax;
+  }
+}
+
+template <int K>
+void launch_gram_solve_t(const StreamArgs &a, const double *partials, double *gram, int method, int max_iter, double c,
+                         const int8_t *order, float *weights, double *aux, hipStream_t s) {
+  hipLaunchKernelGGL(gram_solve_kernel<K>, dim3((unsigned)a.B), dim3(kSumThreads), 0, s, a.K, a.chunk_start,
+                     gram_sum_step(a.K, a.dt, a.N), partials, a.err, method, max_iter, c, order, gram, weights, aux);
+}
+
 template <int K>
 void launch_lane_solve(int B, const double *gram, int method, int max_iter, double c, const int8_t *order,
                        float *weights, double *aux, hipStream_t s) {
@@ -63,6 +123,19 @@ void launch_lane_solve(int B, const double *gram, int method, int max_iter, doub
 }
 
 }  // namespace
+
+hipError_t launch_gram_solve(const StreamArgs &a, const double *partials, double *gram, int method, int max_iter,
+                             double c, const int8_t *order, float *weights, double *aux, hipStream_t s) {
+#define BKMOO_GS_CASE(k) \
+  case k: launch_gram_solve_t<k>(a, partials, gram, method, max_iter, c, order, weights, aux, s); break;
+  switch (a.K) {
+    BKMOO_GS_CASE(2) BKMOO_GS_CASE(3) BKMOO_GS_CASE(4) BKMOO_GS_CASE(5) BKMOO_GS_CASE(6) BKMOO_GS_CASE(7)
+    BKMOO_GS_CASE(8) BKMOO_GS_CASE(9) BKMOO_GS_CASE(10)
+    default: launch_gram_solve_t<0>(a, partials, gram, method, max_iter, c, order, weights, aux, s);
+  }
+#undef BKMOO_GS_CASE
+  return hipGetLastError();
+}
 
 hipError_t launch_solve(int K, int B, const double *gram, int method, int max_iter, double c,
                         const int8_t *order, float *weights, double *aux, hipStream_t s) {
