@@ -357,6 +357,21 @@ int pick_path(int K, int dt, int out_dt, int64_t N, int B, bool vec, int method,
   return BKMOO_PATH_TWO_PASS;
 }
 
+// What the schedule decides the refill kernel's form by (PipePlan).  The
+// rates are those of whole calls on MI355X (bytes of one read and the write
+// for the pipelined form: 4.7 TB/s at K=4 bf16, 4.0 at K=8 bf16 and K=10
+// fp32; both reads and the write for the tiled one).  Pipelined / tiled, us:
+// K=7 bf16 CAGrad, 75 ragged buckets of 25 MiB on average, 901 / 849; K=8
+// bf16 CAGrad, 43 of 29 MiB, 676 / 601.
+constexpr double kPipeBytesPerNs = 4200.0, kTileBytesPerNs = 5200.0;
+constexpr double kPipeHandoffNs = 6000.0, kTileFixedNs = 25000.0;
+
+PipePlan pipe_plan(int K, int dt, int out_dt, int method, int iters, int groups) {
+  const double in = (double)K * elem_bytes(dt), once = in + elem_bytes(out_dt);
+  return PipePlan{groups, once / kPipeBytesPerNs, kPipeHandoffNs + 500.0 * solve_latency_us(method, K, iters),
+                  (once + in) / kTileBytesPerNs, kTileFixedNs};
+}
+
 // bkmoo_resolve's argument checks (everything but the workspace); the
 // 16-byte row phase and whether rows and output allow vector accesses.
 bkmoo_status check_resolve(int32_t K, const void *const *grads, bkmoo_dtype dt, int64_t N, int32_t B,
@@ -421,7 +436,7 @@ bkmoo_status bkmoo_gram(int32_t K, const void *const *grads, bkmoo_dtype dt, int
   if (ws_bytes < L.total) return BKMOO_EWORKSPACE;
   const Carved w = carve(workspace, L);
   hipError_t e = launch_schedule(bucket_offsets, B, N, gram_chunk_elems(K, dt), w.chunk_start,
-                                 w.group_start, w.err, nullptr, 0, stream);
+                                 w.group_start, w.err, nullptr, 0, PipePlan{}, stream);
   if (e != hipSuccess) return BKMOO_EHIP;
   const StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, w.group_start, w.err,
                      shift, vec, g_grid_override.load()};
@@ -457,7 +472,7 @@ bkmoo_status bkmoo_combine(int32_t K, const void *const *grads, bkmoo_dtype dt, 
   if (ws_bytes < L.total) return BKMOO_EWORKSPACE;
   const Carved w = carve(workspace, L);
   hipError_t e = launch_schedule(bucket_offsets, B, N, gram_chunk_elems(K, dt), w.chunk_start,
-                                 nullptr, w.err, nullptr, 0, stream);
+                                 nullptr, w.err, nullptr, 0, PipePlan{}, stream);
   if (e != hipSuccess) return BKMOO_EHIP;
   const StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, nullptr, w.err, shift,
                      vec, g_grid_override.load()};
@@ -516,29 +531,28 @@ bkmoo_status resolve_impl(int32_t K, const void *const *grads, bkmoo_dtype dt, i
   int pgrid = 0;
   const int path = pick_path(K, (int)dt, (int)out_dt, N, B, vec_in && vec_out, (int)method, iters, L.cap_chunks,
                              &pgrid);
-  if (path == BKMOO_PATH_REFILL) {
-    hipError_t e = launch_schedule(bucket_offsets, B, N, gram_chunk_elems(K, dt), w.chunk_start, nullptr,
-                                   w.err, nullptr, 0, stream);
+  if (path != BKMOO_PATH_TWO_PASS) {
+    const int groups = refill_groups(K, (int)dt, N, B);
+    const PipePlan plan = path == BKMOO_PATH_REFILL && g_resolve_path.load() == 0
+                              ? pipe_plan(K, (int)dt, (int)out_dt, (int)method, iters, groups)
+                              : PipePlan{};
+    hipError_t e = launch_schedule(bucket_offsets, B, N, gram_chunk_elems(K, dt), w.chunk_start, nullptr, w.err,
+                                   w.sync, (1 + kFlagCopies) * (int64_t)B * kSyncStride, plan, stream);
     if (e != hipSuccess) return BKMOO_EHIP;
-    e = launch_refill(K, (int)dt, (int)out_dt, grads, bucket_offsets, B, shift, (int)method, iters, c, order,
-                      G, W, aux, out, w.partials, w.sync, w.sync + B * kSyncStride, w.err, g_spin_limit.load(),
-                      pgrid, refill_groups(K, (int)dt, N, B),
-                      refill_temporal_slots(K, (int)dt, pgrid, refill_groups(K, (int)dt, N, B)), stream);
-    return hip_status(e);
-  }
-  if (path == BKMOO_PATH_HYBRID) {
-    const int hgrid = pgrid;
-    hipError_t e = launch_schedule(bucket_offsets, B, N, gram_chunk_elems(K, dt), w.chunk_start,
-                                   nullptr, w.err, w.sync, (1 + kFlagCopies) * (int64_t)B * kSyncStride, stream);
-    if (e != hipSuccess) return BKMOO_EHIP;
-    e = launch_hybrid(K, (int)dt, (int)out_dt, grads, bucket_offsets, B, shift, (int)method, iters, c,
-                      order, G, W, aux, out, w.partials, w.sync, w.sync + B * kSyncStride, w.err, g_spin_limit.load(),
-                      hgrid, hybrid_layout(K, (int)dt, (int)out_dt, (int)method, iters, N, B, hgrid), stream);
+    uint32_t *flags = w.sync + (int64_t)B * kSyncStride;
+    if (path == BKMOO_PATH_REFILL)
+      e = launch_refill(K, (int)dt, (int)out_dt, grads, bucket_offsets, B, shift, (int)method, iters, c, order, G, W,
+                        aux, out, w.partials, w.sync, flags, w.err, g_spin_limit.load(), pgrid, groups,
+                        refill_temporal_slots(K, (int)dt, pgrid, groups), w.chunk_start, stream);
+    else
+      e = launch_hybrid(K, (int)dt, (int)out_dt, grads, bucket_offsets, B, shift, (int)method, iters, c, order, G, W,
+                        aux, out, w.partials, w.sync, flags, w.err, g_spin_limit.load(), pgrid,
+                        hybrid_layout(K, (int)dt, (int)out_dt, (int)method, iters, N, B, pgrid), stream);
     return hip_status(e);
   }
 
   hipError_t e = launch_schedule(bucket_offsets, B, N, gram_chunk_elems(K, dt), w.chunk_start,
-                                 w.group_start, w.err, nullptr, 0, stream);
+                                 w.group_start, w.err, nullptr, 0, PipePlan{}, stream);
   if (e != hipSuccess) return BKMOO_EHIP;
   StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, w.group_start, w.err, shift,
                vec_in, g_grid_override.load()};
@@ -609,6 +623,16 @@ bkmoo_status bkmoo_resolve_traffic(int32_t K, int64_t N, int32_t B, const int64_
     const int g = refill_grid(K, (int)dt, (int)out_dt);
     if (g <= 0) return BKMOO_EUNSUPPORTED;
     const int groups = refill_groups(K, (int)dt, N, B);
+    if (g_resolve_path.load() == 0) {  // the form the schedule would select
+      const PipePlan plan = pipe_plan(K, (int)dt, (int)out_dt, (int)method, max_iter, groups);
+      uint64_t load[kMaxPlanGroups] = {}, most = 0;
+      for (int b = 0; b < B; ++b) load[b % groups] += plan.bucket_ns(offsets_host[b + 1] - offsets_host[b]);
+      for (int q = 0; q < groups; ++q) most = load[q] > most ? load[q] : most;
+      if (plan.tiled(most, N)) {
+        *bytes = once + (uint64_t)K * s * (uint64_t)N;
+        return BKMOO_OK;
+      }
+    }
     const HybLayout lay{(g - refill_solvers(groups)) / groups, 0, 0, 0};
     const int64_t unit = hybrid_unit_elems((int)dt), held_max = refill_held_elems(K, (int)dt, (int)out_dt);
     const int64_t smin = (int64_t)refill_stream_min() * unit;

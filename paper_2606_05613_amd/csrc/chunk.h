@@ -1,0 +1,125 @@
+// One workgroup's work on one chunk of a bucket: its Gram products and its
+// part of the update.  Shared by the two streaming passes and by the tiled
+// form of the cooperative kernels.  Rows at one 16-byte phase.
+#pragma once
+
+#include "combine_impl.h"
+
+namespace bkmoo {
+
+namespace {
+
+// acc[p] += the products of elements [lo, hi), at most U * R vectors a thread.
+template <int K, int DT>
+__device__ __forceinline__ void gram_chunk(const Rows<K> &rows, int64_t lo, int64_t hi, int shift,
+                                           float (&acc)[pairs(K)]) {
+  constexpr int V = vec_elems(DT), EB = elem_bytes(DT);
+  constexpr int R = gram_shape(K).R, U = gram_shape(K).U;
+  const int tid = threadIdx.x;
+  const Split<V> sp(lo, hi, shift);
+  if (tid < sp.nh + sp.nt) {
+    const int64_t n = tid < sp.nh ? lo + tid : sp.hi_a + (tid - sp.nh);
+    float x[K];
+#pragma unroll
+    for (int i = 0; i < K; ++i) x[i] = load_elem<DT>(rows.p[i], n);
+    accumulate<K>(acc, x);
+  }
+#pragma unroll 2
+  for (int u = 0; u < U; ++u) {
+    const int vb = u * kThreads * R + tid;
+    u32x4 buf[R][K];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int v = vb + r * kThreads;
+      if (v < sp.nv) {
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+          buf[r][i] = stream_load(static_cast<const char *>(rows.p[i]) + sp.lo_a * EB, v);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int v = vb + r * kThreads;
+      if (v < sp.nv) {
+        float x[K][V];
+#pragma unroll
+        for (int i = 0; i < K; ++i) decode<DT>(buf[r][i], x[i]);
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+          float xe[K];
+#pragma unroll
+          for (int i = 0; i < K; ++i) xe[i] = x[i][e];
+          accumulate<K>(acc, xe);
+        }
+      }
+    }
+  }
+}
+
+// Lane sums of a workgroup: a fixed xor butterfly across the wavefront
+// (fp32), the wavefronts' sums into red[wave][p] (fp64).
+template <int P>
+__device__ __forceinline__ void reduce_lanes(float (&acc)[P], double (*red)[P]) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+#pragma unroll
+  for (int off = kWave / 2; off >= 1; off >>= 1) {
+#pragma unroll
+    for (int p = 0; p < P; ++p) acc[p] += __shfl_xor(acc[p], off, kWave);
+  }
+  if (lane == 0) {
+#pragma unroll
+    for (int p = 0; p < P; ++p) red[wave][p] = (double)acc[p];
+  }
+}
+
+// The update of elements [lo, hi), at most U * R vectors a thread.
+template <int K, int DT, int ODT, int R, int U>
+__device__ __forceinline__ void combine_chunk(const Rows<K> &rows, int64_t lo, int64_t hi, int shift, const float *w,
+                                              void *out) {
+  constexpr int V = vec_elems(DT), EB = elem_bytes(DT);
+  const int tid = threadIdx.x;
+  const Split<V> sp(lo, hi, shift);
+  if (tid < sp.nh + sp.nt) {
+    const int64_t n = tid < sp.nh ? lo + tid : sp.hi_a + (tid - sp.nh);
+    float x[K];
+#pragma unroll
+    for (int i = 0; i < K; ++i) x[i] = load_elem<DT>(rows.p[i], n);
+    store_elem<ODT>(out, n, wsum<K, ODT>(w, x));
+  }
+#pragma unroll 2
+  for (int u = 0; u < U; ++u) {
+    const int vb = u * kThreads * R + tid;
+    u32x4 buf[R][K];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int v = vb + r * kThreads;
+      if (v < sp.nv) {
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+          buf[r][i] = stream_load(static_cast<const char *>(rows.p[i]) + sp.lo_a * EB, v);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int v = vb + r * kThreads;
+      if (v < sp.nv) {
+        float x[K][V];
+#pragma unroll
+        for (int i = 0; i < K; ++i) decode<DT>(buf[r][i], x[i]);
+        float y[V];
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+          float xe[K];
+#pragma unroll
+          for (int i = 0; i < K; ++i) xe[i] = x[i][e];
+          y[e] = wsum<K, ODT>(w, xe);
+        }
+        store_vec<ODT, V>(out, sp.lo_a + (int64_t)v * V, y);
+      }
+    }
+  }
+}
+
+}  // namespace
+
+}  // namespace bkmoo

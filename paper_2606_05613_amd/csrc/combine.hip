@@ -20,7 +20,7 @@
 // rounds once: fp64 -> fp32 with round-to-odd, then RNE to bf16.  Rounding
 // to odd into a format with at least two more significand bits than the
 // target makes the second rounding the correct single rounding.
-#include "combine_impl.h"
+#include "chunk.h"
 
 namespace bkmoo {
 
@@ -30,11 +30,7 @@ template <int K, int DT, int ODT>
 __global__ __launch_bounds__(kThreads) void combine_kernel(
     Rows<K> rows, const int64_t *__restrict__ offs, const int64_t *__restrict__ cs, int B,
     int shift, int vec, const float *__restrict__ weights, void *out) {
-  constexpr int V = vec_elems(DT);
-  constexpr int R = combine_shape(K).R;
-  constexpr int U = combine_shape(K).U;
   constexpr int64_t C = combine_chunk_elems(K, DT);
-  constexpr int EB = elem_bytes(DT);
 
   const int64_t total = cs[B] * kCombineParts;
   const int tid = threadIdx.x;
@@ -49,46 +45,7 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(
     for (int i = 0; i < K; ++i) w[i] = weights[(int64_t)b * K + i];
 
     if (vec) {
-      const Split<V> sp(lo, hi, shift);
-      if (tid < sp.nh + sp.nt) {
-        const int64_t n = tid < sp.nh ? lo + tid : sp.hi_a + (tid - sp.nh);
-        float x[K];
-#pragma unroll
-        for (int i = 0; i < K; ++i) x[i] = load_elem<DT>(rows.p[i], n);
-        store_elem<ODT>(out, n, wsum<K, ODT>(w, x));
-      }
-#pragma unroll 2
-      for (int u = 0; u < U; ++u) {
-        const int vb = u * kThreads * R + tid;
-        u32x4 buf[R][K];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const int v = vb + r * kThreads;
-          if (v < sp.nv) {
-#pragma unroll
-            for (int i = 0; i < K; ++i)
-              buf[r][i] = stream_load(static_cast<const char *>(rows.p[i]) + sp.lo_a * EB, v);
-          }
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const int v = vb + r * kThreads;
-          if (v < sp.nv) {
-            float x[K][V];
-#pragma unroll
-            for (int i = 0; i < K; ++i) decode<DT>(buf[r][i], x[i]);
-            float y[V];
-#pragma unroll
-            for (int e = 0; e < V; ++e) {
-              float xe[K];
-#pragma unroll
-              for (int i = 0; i < K; ++i) xe[i] = x[i][e];
-              y[e] = wsum<K, ODT>(w, xe);
-            }
-            store_vec<ODT, V>(out, sp.lo_a + (int64_t)v * V, y);
-          }
-        }
-      }
+      combine_chunk<K, DT, ODT, combine_shape(K).R, combine_shape(K).U>(rows, lo, hi, shift, w, out);
     } else {
       for (int64_t n = lo + tid; n < hi; n += kThreads) {
         float x[K];

@@ -51,6 +51,37 @@ __device__ __forceinline__ T load_agent(const T *p) {
   return __hip_atomic_load(const_cast<T *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// A weight in a record of K words: its bits inverted, so that a record the
+// schedule has cleared holds none (a NaN is stored as the default one, whose
+// inverse is not zero either).
+__device__ __forceinline__ uint32_t weight_word(float w) { return ~(w == w ? __float_as_uint(w) : 0x7fc00000u); }
+__device__ __forceinline__ float word_weight(uint32_t x) { return __uint_as_float(~x); }
+
+__device__ __forceinline__ void note_timeout(uint32_t *err) {
+  __hip_atomic_fetch_or(err, kErrTimeout, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Bounded poll of a weight record until none of its K words is zero; x
+// receives the words.  SLEEP x 64 cycles between polls.
+template <int K, int SLEEP>
+__device__ bool poll_record(const uint32_t *rec, uint32_t (&x)[K], uint32_t *err, uint32_t spin_limit) {
+  uint32_t spins = 0;
+  for (;;) {
+    bool ready = true;
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      x[i] = load_agent(rec + i);
+      ready = ready && x[i] != 0u;
+    }
+    if (ready) return true;
+    __builtin_amdgcn_s_sleep(SLEEP);
+    if (++spins >= spin_limit) {
+      note_timeout(err);
+      return false;
+    }
+  }
+}
+
 }  // namespace
 
 }  // namespace bkmoo

@@ -18,8 +18,8 @@
 // consecutive chunks first, then the groups); a resolve call adds them in
 // the kernel that also solves the bucket's problem (solve.hip).  No atomics:
 // the result is bitwise independent of the grid and of scheduling.
+#include "chunk.h"
 #include "gram_sum.h"
-#include "stream_common.h"
 
 namespace bkmoo {
 
@@ -29,19 +29,15 @@ template <int K, int DT>
 __global__ __launch_bounds__(kThreads) void gram_partial_kernel(
     Rows<K> rows, const int64_t *__restrict__ offs, const int64_t *__restrict__ cs, int B,
     int shift, int vec, double *__restrict__ partials) {
-  constexpr int V = vec_elems(DT);
-  constexpr int R = gram_shape(K).R;
-  constexpr int U = gram_shape(K).U;
   constexpr int64_t C = gram_chunk_elems(K, DT);
   constexpr int P = pairs(K);
-  constexpr int EB = elem_bytes(DT);
   __shared__ double red[kThreads / kWave][P];
 
   int64_t c, cend;
   my_chunks(cs[B], c, cend);
   if (c >= cend) return;
   int b = find_bucket(cs, B, c);
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int tid = threadIdx.x;
 
   for (; c < cend; ++c) {
     while (cs[b + 1] <= c) ++b;
@@ -53,44 +49,7 @@ __global__ __launch_bounds__(kThreads) void gram_partial_kernel(
     for (int p = 0; p < P; ++p) acc[p] = 0.0f;
 
     if (vec) {
-      const Split<V> sp(lo, hi, shift);
-      if (tid < sp.nh + sp.nt) {
-        const int64_t n = tid < sp.nh ? lo + tid : sp.hi_a + (tid - sp.nh);
-        float x[K];
-#pragma unroll
-        for (int i = 0; i < K; ++i) x[i] = load_elem<DT>(rows.p[i], n);
-        accumulate<K>(acc, x);
-      }
-#pragma unroll 2
-      for (int u = 0; u < U; ++u) {
-        const int vb = u * kThreads * R + tid;
-        u32x4 buf[R][K];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const int v = vb + r * kThreads;
-          if (v < sp.nv) {
-#pragma unroll
-            for (int i = 0; i < K; ++i)
-              buf[r][i] = stream_load(static_cast<const char *>(rows.p[i]) + sp.lo_a * EB, v);
-          }
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const int v = vb + r * kThreads;
-          if (v < sp.nv) {
-            float x[K][V];
-#pragma unroll
-            for (int i = 0; i < K; ++i) decode<DT>(buf[r][i], x[i]);
-#pragma unroll
-            for (int e = 0; e < V; ++e) {
-              float xe[K];
-#pragma unroll
-              for (int i = 0; i < K; ++i) xe[i] = x[i][e];
-              accumulate<K>(acc, xe);
-            }
-          }
-        }
-      }
+      gram_chunk<K, DT>(rows, lo, hi, shift, acc);
     } else {
       for (int64_t n = lo + tid; n < hi; n += kThreads) {
         float x[K];
@@ -100,17 +59,8 @@ __global__ __launch_bounds__(kThreads) void gram_partial_kernel(
       }
     }
 
-    // fixed-order reduction: xor butterfly across the wavefront (fp32),
-    // then the 4 wavefronts in order in fp64
-#pragma unroll
-    for (int off = kWave / 2; off >= 1; off >>= 1) {
-#pragma unroll
-      for (int p = 0; p < P; ++p) acc[p] += __shfl_xor(acc[p], off, kWave);
-    }
-    if (lane == 0) {
-#pragma unroll
-      for (int p = 0; p < P; ++p) red[wave][p] = (double)acc[p];
-    }
+    // fixed-order reduction: then the 4 wavefronts in order
+    reduce_lanes<P>(acc, red);
     __syncthreads();
     for (int p = tid; p < P; p += kThreads) {
       double s = red[0][p];

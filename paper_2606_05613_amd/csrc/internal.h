@@ -83,7 +83,7 @@ constexpr int64_t kSyncStride = 32;  // uint32 words
 constexpr int kFlagCopies = 8;
 
 // Workspace layout (every region 256-byte aligned):
-//   [0, 256)            header: uint32 error word at byte 0
+//   [0, 256)            header: uint32 error word at byte 0, the tiled-form word at byte 4
 //   chunk_start         int64 [B + 1]     (prefix sum of chunks per bucket)
 //   gram                fp64  [B][K][K]   (used when the caller passes none)
 //   weights             fp32  [B][K]      (used when the caller passes none)
@@ -127,6 +127,35 @@ inline Layout layout(int K, int64_t N, int B, int dt) {
 constexpr uint32_t kErrOffsets = 0x1u;
 constexpr uint32_t kErrTimeout = 0x2u;
 
+// Whether the refill kernel runs its pipelined or its tiled form, decided
+// where the bucket sizes are known: on the device, from the offsets.
+//
+// The pipelined form deals bucket b to group b % groups of the workgroups,
+// which the host can only size by the average bucket.  Where sizes differ,
+// one group's buckets can outlast the others' by far (GPT-2 with a bucket per
+// tensor, K=4 bf16: the 38.6M-element embedding of 124M on 17 of 512
+// workgroups, 1.70 ms against 0.51 tiled), and a small bucket costs a hand-off
+// whatever its size.  The tiled form reads everything twice but spreads every
+// bucket over the chip.  Estimates, from times on MI355X: a bucket takes
+// elem_ns an element on the whole chip (its group has 1/groups of that) and at
+// least a hand-off; the tiled form tile_elem_ns an element and tile_fixed_ns.
+// (The two-buffer kernel spreads every bucket over the chip as it is; on
+// ragged buckets it stays within a few percent of two reads: K=8 bf16, 11
+// to 45 buckets of 125-240 MiB on average, 0.95 to 1.10 times the two passes'
+// speed.)
+constexpr int kMaxPlanGroups = 32;
+struct PipePlan {
+  int groups;  // 0: no plan (another kernel, or the path is forced)
+  double elem_ns, handoff_ns, tile_elem_ns, tile_fixed_ns;
+  __host__ __device__ uint64_t bucket_ns(int64_t n) const {
+    const double t = (double)n * elem_ns * groups;
+    return n == 0 ? 0 : (uint64_t)(t > handoff_ns ? t : handoff_ns);
+  }
+  __host__ __device__ bool tiled(uint64_t longest_group_ns, int64_t N) const {
+    return (double)longest_group_ns > 1.1 * ((double)N * tile_elem_ns + tile_fixed_ns);
+  }
+};
+
 // Pointers of the K task rows, passed by value as kernel arguments.
 template <int K>
 struct Rows {
@@ -151,11 +180,11 @@ struct StreamArgs {
 };
 
 // Validates offsets, writes chunk_start for chunks of C elements (and, if
-// group_start is not null, the prefix of finalize groups), clears the error
-// word and zeroes `nsync` words at `sync` (may be null).
+// group_start is not null, the prefix of finalize groups), sets the error
+// word and, by `plan`, the word after it, and zeroes `nsync` words at `sync`.
 hipError_t launch_schedule(const int64_t *offsets, int B, int64_t N, int64_t C, int64_t *chunk_start,
                            int64_t *group_start, uint32_t *err, uint32_t *sync, int64_t nsync,
-                           hipStream_t s);
+                           const PipePlan &plan, hipStream_t s);
 // Gram pass: per-chunk partials (and group sums, left in the slots of the
 // groups' first chunks), then the per-bucket matrices.  gram_sum_step is the
 // distance of the slots that the finalize adds up (1: the chunks).

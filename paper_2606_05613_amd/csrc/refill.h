@@ -27,6 +27,6 @@ hipError_t launch_refill(int K, int dt, int out_dt, const void *const *rows, con
                          int shift, int method, int iters, double c, const int8_t *order, double *gram,
                          float *weights, double *aux, void *out, double *partials, uint32_t *arrive,
                          uint32_t *recs, uint32_t *err, uint32_t spin_limit, int grid, int groups,
-                         int tslots, hipStream_t s);
+                         int tslots, const int64_t *chunk_start, hipStream_t s);
 
 }  // namespace bkmoo

@@ -32,10 +32,10 @@
 // agent-scope stores, waits for them (publish point) and bumps the bucket's
 // arrival counter; the bucket's solver waits for every segment's arrival,
 // adds the partials in a fixed order, solves on one wavefront and stores the
-// K weights with agent-scope stores into kFlagCopies records that were
-// filled with "pending" marks (signalling NaNs, which no conversion
-// produces) before the launch; data workgroup w polls record w % kFlagCopies
-// until no weight is pending, so the weights arrive with the poll.  Two sets
+// K weights (as words that are never zero) with agent-scope stores into
+// kFlagCopies records that were cleared before the launch; data workgroup w
+// polls record w % kFlagCopies until no word is zero, so the weights arrive
+// with the poll.  Two sets
 // of partial slots suffice (bucket b uses set b & 1): a data workgroup
 // writes bucket b+2's partial after it has seen bucket b's weights (it
 // waits for them in the period before), which the solver stores only after
@@ -45,6 +45,9 @@
 // publishes NaN weights, a data workgroup whose wait runs out combines with
 // NaN weights, and both set the error word's timeout bit.
 //
+// Where the buckets' sizes make this split a bad one the schedule selects the
+// tiled form instead (tiled.h, PipePlan).
+//
 // No cycle of waits: bucket b's weights need every arrival for b, and a data
 // workgroup arrives for b right after its wait for bucket b-1's weights;
 // solvers wait only for arrivals; the cooperative launch keeps every
@@ -53,6 +56,7 @@
 #include "coop_common.h"
 #include "refill.h"
 #include "solve_impl.h"
+#include "tiled.h"
 
 namespace bkmoo {
 
@@ -62,10 +66,6 @@ constexpr int kRefThreads = 256;  // two workgroups per CU
 constexpr int kRefWaves = kRefThreads / kWave;
 constexpr int kRefMaxSlots = 512;  // segment slots (data workgroups) per bucket at most
 constexpr int kRefMaxSlotsEst = 508;  // data workgroups of a 256-CU device
-// Pending mark of a weight: a signalling NaN with payload 1, which an fp64
-// -> fp32 conversion never produces (a NaN comes out quiet).
-constexpr uint32_t kWeightPending = 0x7f800001u;
-
 // Vectors per task row and thread kept on chip (registers NR, LDS NL),
 // streamed per row and step (NS), and kept slots between a refill load and
 // the addition of its products (lag): the registers and LDS the two-buffer
@@ -109,6 +109,7 @@ constexpr int ref_red_batch(int ng) { return (kRefMaxSlotsEst + ng - 1) / ng < 2
 
 struct RefArgs {
   const int64_t *offs;  // [B+1]
+  const int64_t *cs;    // [B+1] chunk prefix (tiled form)
   int B;
   int shift;
   int method, iters;
@@ -120,7 +121,7 @@ struct RefArgs {
   void *out;
   double *partials;  // [2][nslots][P rounded up to even]
   uint32_t *arrive;  // [B] at stride kSyncStride, zero at launch (hint)
-  uint32_t *recs;    // [kFlagCopies][B] records of K weights at stride kSyncStride, pending-marked
+  uint32_t *recs;    // [kFlagCopies][B] records of K weights at stride kSyncStride, zero at launch
   uint32_t *err;
   uint32_t spin_limit;
   HybLayout lay;     // segment slots of one group (equal segments)
@@ -134,31 +135,6 @@ constexpr int kCoherent = 16;
 
 __device__ __forceinline__ u32x4 buf_load16_keep(Rsrc r, uint32_t voff, uint32_t soff) {
   return __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0);
-}
-
-__device__ __forceinline__ void note_timeout(const RefArgs &a) {
-  __hip_atomic_fetch_or(a.err, kErrTimeout, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Bounded poll of a weight record until none of its K words is pending;
-// x receives the words.  SLEEP x 64 cycles between polls.
-template <int K, int SLEEP>
-__device__ bool poll_record(const uint32_t *rec, uint32_t (&x)[K], const RefArgs &a) {
-  uint32_t spins = 0;
-  for (;;) {
-    bool ready = true;
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      x[i] = load_agent(rec + i);
-      ready = ready && x[i] != kWeightPending;
-    }
-    if (ready) return true;
-    __builtin_amdgcn_s_sleep(SLEEP);
-    if (++spins >= a.spin_limit) {
-      note_timeout(a);
-      return false;
-    }
-  }
 }
 
 template <int K, int DT, int ODT>
@@ -426,9 +402,10 @@ struct Refill {
     const int t = threadIdx.x;
     if (t == 0) {
       uint32_t x[K];
-      const bool ok = poll_record<K, 32>(a.recs + ((int64_t)(w % kFlagCopies) * a.B + b) * kSyncStride, x, a);
+      const bool ok = poll_record<K, 32>(a.recs + ((int64_t)(w % kFlagCopies) * a.B + b) * kSyncStride, x, a.err,
+                                         a.spin_limit);
 #pragma unroll
-      for (int i = 0; i < K; ++i) sm.wsh[par(a, b)][i] = ok ? __uint_as_float(x[i]) : __builtin_nanf("");
+      for (int i = 0; i < K; ++i) sm.wsh[par(a, b)][i] = ok ? word_weight(x[i]) : __builtin_nanf("");
     }
     __syncthreads();
 #pragma unroll
@@ -437,7 +414,7 @@ struct Refill {
 
   // Data workgroup w: group w % groups, slot w / groups of that group's
   // buckets (none when the grid does not divide evenly).
-  static __device__ void data(const Rows<K> &rows, const RefArgs &a, Smem &sm, int w) {
+  static __device__ __forceinline__ void data(const Rows<K> &rows, const RefArgs &a, Smem &sm, int w) {
     const int G = a.groups, grp = w % G, slot = w / G;
     if (slot >= a.lay.nslots || grp >= a.B) return;
     u32x4 reg[NR][K];
@@ -481,7 +458,7 @@ struct Refill {
   }
 
   // Solver workgroup j: buckets j, j + nsolv, ...
-  static __device__ void solve(const RefArgs &a, Smem &sm, int j) {
+  static __device__ __forceinline__ void solve(const RefArgs &a, Smem &sm, int j) {
     const int t = threadIdx.x, wave = t / kWave;
     // a solve sits on the critical path of every data workgroup and shares
     // its CU with one: its waves go first
@@ -496,7 +473,7 @@ struct Refill {
         while (load_agent(&a.arrive[(int64_t)b * kSyncStride]) < (uint32_t)nseg) {
           __builtin_amdgcn_s_sleep(1);
           if (++spins >= a.spin_limit) {
-            note_timeout(a);
+            note_timeout(a.err);
             ok = false;
             break;
           }
@@ -571,7 +548,7 @@ struct Refill {
         if (t < kFlagCopies) {
           uint32_t *rec = a.recs + ((int64_t)t * a.B + b) * kSyncStride;
 #pragma unroll
-          for (int i = 0; i < K; ++i) store_agent(rec + i, __float_as_uint(wk[i]));
+          for (int i = 0; i < K; ++i) store_agent(rec + i, weight_word(wk[i]));
         }
         if (t == 0) {
 #pragma unroll
@@ -590,7 +567,12 @@ struct Refill {
 template <int K, int DT, int ODT>
 __global__ __launch_bounds__(kRefThreads, 2) void refill_kernel(Rows<K> rows, RefArgs a) {
   using R = Refill<K, DT, ODT>;
-  __shared__ typename R::Smem sm;
+  using Td = Tiled<K, DT, ODT>;
+  __shared__ union {
+    typename R::Smem sm;
+    typename Td::Smem tiled;
+  } lds;
+  typename R::Smem &sm = lds.sm;
   // the solvers are the lowest block indices: dispatched first, they are the
   // older workgroup on their CU, which the wave arbiter favours
   const int w = (int)blockIdx.x - a.nsolv;
@@ -606,19 +588,17 @@ __global__ __launch_bounds__(kRefThreads, 2) void refill_kernel(Rows<K> rows, Re
     }
     return;
   }
+  if (a.err[1]) {
+    const TileArgs ta{a.offs, a.cs, a.B, a.shift, a.method, a.iters, a.c, a.order, a.gram, a.weights, a.aux, a.out,
+                      a.partials, a.arrive, a.recs, a.err, a.spin_limit, a.nsolv};
+    Td::run(rows, ta, lds.tiled);
+    return;
+  }
   if (w < 0) {
     R::solve(a, sm, (int)blockIdx.x);
     return;
   }
   R::data(rows, a, sm, w);
-}
-
-// Zero arrival counters, pending marks in the weight records.
-__global__ void refill_init_kernel(uint32_t *arrive, int64_t narrive, uint32_t *recs, int64_t nrec) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < narrive; i += stride) arrive[i] = 0u;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nrec; i += stride)
-    recs[i] = kWeightPending;
 }
 
 template <int K, int DT, int ODT>
@@ -688,16 +668,12 @@ hipError_t launch_refill(int K, int dt, int out_dt, const void *const *rows, con
                          int shift, int method, int iters, double c, const int8_t *order, double *gram,
                          float *weights, double *aux, void *out, double *partials, uint32_t *arrive,
                          uint32_t *recs, uint32_t *err, uint32_t spin_limit, int grid, int groups,
-                         int tslots, hipStream_t s) {
+                         int tslots, const int64_t *chunk_start, hipStream_t s) {
   const int nsolv = refill_solvers(groups);
   if (groups < 1 || grid - nsolv < groups) return hipErrorInvalidValue;
   const HybLayout lay{(grid - nsolv) / groups, 0, 0, 0};
-  const RefArgs a{offs, B, shift, method, iters, c, order, gram, weights, aux, out, partials, arrive, recs,
+  const RefArgs a{offs, chunk_start, B, shift, method, iters, c, order, gram, weights, aux, out, partials, arrive, recs,
                   err, spin_limit, lay, nsolv, groups, tslots};
-  hipLaunchKernelGGL(refill_init_kernel, dim3(64), dim3(256), 0, s, arrive, (int64_t)B * kSyncStride, recs,
-                     (int64_t)kFlagCopies * B * kSyncStride);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
 #define BKMOO_REF_CASE(k)                                                                        \
   case k:                                                                                        \
     if (dt == F32)                                                                               \
