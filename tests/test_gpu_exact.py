@@ -42,6 +42,46 @@ def _grams(k, nb, seed):
     return np.stack(out)
 
 
+def _near_ties(k, nb, seed):
+    """Gram matrices near the lines where a support is kept or not: a last
+    task placed so that the minimum-norm point's inner product with it exceeds
+    the point's squared norm by a relative +-1e-14 .. 1e-3 (its weight or its
+    slack is about that), task norms over up to eight decades, and a pair of
+    tasks at a relative distance of 1e-1 .. 1e-9 from each other."""
+    rng = np.random.default_rng(seed)
+    out = []
+    for b in range(nb):
+        n = 4 * k
+        x = rng.standard_normal((k, n))
+        x[:-1] += 0.7 * rng.standard_normal(n)
+        kind = b % 3
+        if kind == 0:
+            a = np.linalg.solve(x[:-1] @ x[:-1].T, np.ones(k - 1))
+            p = (a / a.sum()) @ x[:-1]  # nearest point of the others' affine hull
+            slack = rng.choice([-1.0, 1.0]) * 10.0 ** rng.uniform(-14, -3)
+            x[-1] += (p @ p * (1.0 + slack) - x[-1] @ p) / (p @ p) * p
+        elif kind == 1:
+            x *= 10.0 ** rng.uniform(-4, 4, size=(k, 1))
+        else:
+            x[-1] = x[0] + 10.0 ** rng.uniform(-9, -1) * x[-1]
+        out.append(x @ x.T)
+    return np.stack(out)
+
+
+@pytest.mark.parametrize("method", ["mgda", "cagrad"])
+@pytest.mark.parametrize("K", [2, 3, 6, 7, 9, 10])
+def test_exact_solvers_near_ties(gpu_lib, K, method):
+    """Both kernels of the exact solve: buckets that the first one must not
+    answer by itself among buckets that it does."""
+    G = _near_ties(K, 60, 3500 + K)
+    print(f"case exact near ties {method} K={K}", flush=True)
+    W, A = gpu_lib.solve(torch.from_numpy(G).cuda(), f"{method}-exact", cagrad_c=0.5)
+    torch.cuda.synchronize()
+    w_ora, a_ora = oracle.solve(G, method, cagrad_c=0.5, exact=True)
+    _compare(G, W.cpu().numpy().astype(np.float64), A.cpu().numpy(), w_ora, a_ora, method,
+             f"{method}-exact near ties K={K}")
+
+
 @pytest.mark.parametrize("method", ["mgda", "cagrad"])
 @pytest.mark.parametrize("K", [2, 3, 4, 5, 6, 8, 10])
 def test_exact_solvers_stage_isolated(gpu_lib, K, method):
