@@ -38,8 +38,9 @@
  *   - grads is a HOST array of K device pointers, one per task, each to N
  *     elements of dtype `dt`.  A contiguous [K][N] buffer is passed as
  *     base + i*N*elem_size.  Rows need natural alignment (4 bytes for f32,
- *     2 for bf16); 16-byte alignment of every row at the same phase enables
- *     128-bit loads, otherwise a scalar path is used.
+ *     2 for bf16).  128-bit accesses are used throughout; rows (and output)
+ *     at one 16-byte phase get aligned ones and may take the cooperative
+ *     kernels.
  *   - bucket_offsets is int64[B+1] in device memory with o_0 = 0, o_B = N and
  *     o_b <= o_{b+1} (empty buckets are allowed).  Offsets are checked on the
  *     device; invalid offsets set BKMOO_DEVERR_OFFSETS in the workspace error

@@ -52,9 +52,9 @@ bkmoo_status check_shape(int32_t K, int64_t N, int32_t B, int dt) {
   return BKMOO_OK;
 }
 
-// Row pointers: non-null, naturally aligned.  128-bit loads need every row
-// at the same 16-byte phase; `shift` is then the first element index whose
-// address is 16-byte aligned, modulo the vector width.
+// Row pointers: non-null, naturally aligned.  `shift` is the first element
+// index whose address in row 0 is 16-byte aligned, modulo the vector width;
+// *vec: every row is at the same 16-byte phase, so that it is in all of them.
 bkmoo_status check_rows(int32_t K, const void *const *grads, int dt, int64_t N, int *shift,
                         bool *vec) {
   if (!grads) return BKMOO_EINVAL;
@@ -73,8 +73,11 @@ bkmoo_status check_rows(int32_t K, const void *const *grads, int dt, int64_t N, 
 
 bool overlaps(uintptr_t a, size_t na, uintptr_t b, size_t nb) { return a < b + nb && b < a + na; }
 
+// Also where the combine's vectors start (out_shift): with the rows, if the
+// output's vector stores are aligned there; else where they are, and *vec is
+// cleared.
 bkmoo_status check_out(int32_t K, const void *const *grads, int dt, int64_t N, const void *out,
-                       int out_dt, int shift, bool *vec) {
+                       int out_dt, int shift, bool *vec, int *out_shift) {
   if (!valid_dtype(out_dt)) return BKMOO_EINVAL;
   const uintptr_t o = (uintptr_t)out;
   const uintptr_t eo = (uintptr_t)elem_bytes(out_dt);
@@ -88,6 +91,7 @@ bkmoo_status check_out(int32_t K, const void *const *grads, int dt, int64_t N, c
   // vector stores: V outputs at out + (shift + m V) * s_out, 8 or 16 bytes wide
   const uintptr_t width = (uintptr_t)vec_elems(dt) * eo < 16 ? (uintptr_t)vec_elems(dt) * eo : 16;
   if ((o + (uintptr_t)shift * eo) % width != 0) *vec = false;
+  *out_shift = *vec ? shift : (int)((width - o % width) % width / eo);
   return BKMOO_OK;
 }
 
@@ -373,15 +377,15 @@ PipePlan pipe_plan(int K, int dt, int out_dt, int method, int iters, int groups)
 }
 
 // bkmoo_resolve's argument checks (everything but the workspace); the
-// 16-byte row phase and whether rows and output allow vector accesses.
+// 16-byte row phase, whether rows and output share one (the cooperative
+// kernels need that) and where the combine's vectors start.
 bkmoo_status check_resolve(int32_t K, const void *const *grads, bkmoo_dtype dt, int64_t N, int32_t B,
                            const int64_t *bucket_offsets, bkmoo_method method, const bkmoo_hparams *hp,
-                           const void *out, bkmoo_dtype out_dt, int *shift, bool *vec_in, bool *vec_out) {
+                           const void *out, bkmoo_dtype out_dt, int *shift, bool *vec, int *out_shift) {
   bkmoo_status st = check_shape(K, N, B, dt);
   if (st != BKMOO_OK) return st;
-  if ((st = check_rows(K, grads, dt, N, shift, vec_in)) != BKMOO_OK) return st;
-  *vec_out = *vec_in;
-  if ((st = check_out(K, grads, dt, N, out, out_dt, *shift, vec_out)) != BKMOO_OK) return st;
+  if ((st = check_rows(K, grads, dt, N, shift, vec)) != BKMOO_OK) return st;
+  if ((st = check_out(K, grads, dt, N, out, out_dt, *shift, vec, out_shift)) != BKMOO_OK) return st;
   if ((st = check_hparams(method, hp)) != BKMOO_OK) return st;
   if (k_unsupported(K, method)) return BKMOO_EUNSUPPORTED;
   return bucket_offsets ? BKMOO_OK : BKMOO_EINVAL;
@@ -439,7 +443,7 @@ bkmoo_status bkmoo_gram(int32_t K, const void *const *grads, bkmoo_dtype dt, int
                                  w.group_start, w.err, nullptr, 0, PipePlan{}, stream);
   if (e != hipSuccess) return BKMOO_EHIP;
   const StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, w.group_start, w.err,
-                     shift, vec, g_grid_override.load()};
+                     shift, g_grid_override.load()};
   if (launch_gram_partials(a, w.partials, stream) != hipSuccess) return BKMOO_EHIP;
   return hip_status(launch_gram_finalize(a, w.partials, gram, stream));
 }
@@ -466,7 +470,8 @@ bkmoo_status bkmoo_combine(int32_t K, const void *const *grads, bkmoo_dtype dt, 
   int shift = 0;
   bool vec = false;
   if ((st = check_rows(K, grads, dt, N, &shift, &vec)) != BKMOO_OK) return st;
-  if ((st = check_out(K, grads, dt, N, out, out_dt, shift, &vec)) != BKMOO_OK) return st;
+  int out_shift = 0;
+  if ((st = check_out(K, grads, dt, N, out, out_dt, shift, &vec, &out_shift)) != BKMOO_OK) return st;
   if (!bucket_offsets || !weights || !workspace) return BKMOO_EINVAL;
   const Layout L = layout(K, N, B, dt);
   if (ws_bytes < L.total) return BKMOO_EWORKSPACE;
@@ -474,8 +479,8 @@ bkmoo_status bkmoo_combine(int32_t K, const void *const *grads, bkmoo_dtype dt, 
   hipError_t e = launch_schedule(bucket_offsets, B, N, gram_chunk_elems(K, dt), w.chunk_start,
                                  nullptr, w.err, nullptr, 0, PipePlan{}, stream);
   if (e != hipSuccess) return BKMOO_EHIP;
-  const StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, nullptr, w.err, shift,
-                     vec, g_grid_override.load()};
+  const StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, nullptr, w.err, out_shift,
+                     g_grid_override.load()};
   return hip_status(launch_combine(a, weights, out, (int)out_dt, stream));
 }
 
@@ -492,10 +497,10 @@ bkmoo_status bkmoo_resolve_noalloc(int32_t K, const void *const *grads, bkmoo_dt
                                    int32_t B, const int64_t *bucket_offsets, bkmoo_method method,
                                    const bkmoo_hparams *hp, void *out, bkmoo_dtype out_dt, double *gram,
                                    float *weights, double *aux, hipStream_t stream) {
-  int shift = 0;
-  bool vec_in = false, vec_out = false;
+  int shift = 0, out_shift = 0;
+  bool vec = false;
   const bkmoo_status st = check_resolve(K, grads, dt, N, B, bucket_offsets, method, hp, out, out_dt, &shift,
-                                        &vec_in, &vec_out);
+                                        &vec, &out_shift);
   if (st != BKMOO_OK) return st;
   if (layout(K, N, B, dt).total > kScratchBytes) return BKMOO_EWORKSPACE;
   void *ws = scratch_on_current_device();
@@ -513,10 +518,10 @@ bkmoo_status resolve_impl(int32_t K, const void *const *grads, bkmoo_dtype dt, i
                           const int64_t *bucket_offsets, bkmoo_method method, const bkmoo_hparams *hp,
                           void *out, bkmoo_dtype out_dt, double *gram, float *weights, double *aux,
                           void *workspace, size_t ws_bytes, hipStream_t stream) {
-  int shift = 0;
-  bool vec_in = false, vec_out = false;
+  int shift = 0, out_shift = 0;
+  bool vec = false;
   const bkmoo_status st = check_resolve(K, grads, dt, N, B, bucket_offsets, method, hp, out, out_dt, &shift,
-                                        &vec_in, &vec_out);
+                                        &vec, &out_shift);
   if (st != BKMOO_OK) return st;
   if (!workspace) return BKMOO_EINVAL;
   const Layout L = layout(K, N, B, dt);
@@ -529,7 +534,7 @@ bkmoo_status resolve_impl(int32_t K, const void *const *grads, bkmoo_dtype dt, i
   const int8_t *order = hp ? hp->pcgrad_order : nullptr;
 
   int pgrid = 0;
-  const int path = pick_path(K, (int)dt, (int)out_dt, N, B, vec_in && vec_out, (int)method, iters, L.cap_chunks,
+  const int path = pick_path(K, (int)dt, (int)out_dt, N, B, vec, (int)method, iters, L.cap_chunks,
                              &pgrid);
   if (path != BKMOO_PATH_TWO_PASS) {
     const int groups = refill_groups(K, (int)dt, N, B);
@@ -555,7 +560,7 @@ bkmoo_status resolve_impl(int32_t K, const void *const *grads, bkmoo_dtype dt, i
                                  w.group_start, w.err, nullptr, 0, PipePlan{}, stream);
   if (e != hipSuccess) return BKMOO_EHIP;
   StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, w.group_start, w.err, shift,
-               vec_in, g_grid_override.load()};
+               g_grid_override.load()};
   if (launch_gram_partials(a, w.partials, stream) != hipSuccess) return BKMOO_EHIP;
   if (is_exact(method)) {
     if (launch_gram_finalize(a, w.partials, G, stream) != hipSuccess) return BKMOO_EHIP;
@@ -564,7 +569,7 @@ bkmoo_status resolve_impl(int32_t K, const void *const *grads, bkmoo_dtype dt, i
     e = launch_gram_solve(a, w.partials, G, (int)method, iters, c, order, W, aux, stream);
   }
   if (e != hipSuccess) return BKMOO_EHIP;
-  a.vec = vec_out;
+  a.shift = out_shift;
   return hip_status(launch_combine(a, W, out, (int)out_dt, stream));
 }
 

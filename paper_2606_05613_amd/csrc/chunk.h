@@ -1,6 +1,10 @@
 // One workgroup's work on one chunk of a bucket: its Gram products and its
 // part of the update.  Shared by the two streaming passes and by the tiled
-// form of the cooperative kernels.  Rows at one 16-byte phase.
+// form of the refill kernel.  Vectors start where `shift` puts them, on
+// 16-byte boundaries of the rows where these share a phase; rows at other
+// phases are read with 128-bit loads all the same.  Read element by element,
+// as such rows were before, K=3 bf16, 30M elements in odd-length rows, took
+// 149 us a step (now 100), K=8 bf16 of 90M 890 us (366).
 #pragma once
 
 #include "combine_impl.h"

@@ -29,11 +29,10 @@ namespace {
 template <int K, int DT, int ODT>
 __global__ __launch_bounds__(kThreads) void combine_kernel(
     Rows<K> rows, const int64_t *__restrict__ offs, const int64_t *__restrict__ cs, int B,
-    int shift, int vec, const float *__restrict__ weights, void *out) {
+    int shift, const float *__restrict__ weights, void *out) {
   constexpr int64_t C = combine_chunk_elems(K, DT);
 
   const int64_t total = cs[B] * kCombineParts;
-  const int tid = threadIdx.x;
 
   for (int64_t c = blockIdx.x; c < total; c += gridDim.x) {
     const int b = find_bucket(cs, B, c / kCombineParts);
@@ -44,16 +43,7 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(
 #pragma unroll
     for (int i = 0; i < K; ++i) w[i] = weights[(int64_t)b * K + i];
 
-    if (vec) {
-      combine_chunk<K, DT, ODT, combine_shape(K).R, combine_shape(K).U>(rows, lo, hi, shift, w, out);
-    } else {
-      for (int64_t n = lo + tid; n < hi; n += kThreads) {
-        float x[K];
-#pragma unroll
-        for (int i = 0; i < K; ++i) x[i] = load_elem<DT>(rows.p[i], n);
-        store_elem<ODT>(out, n, wsum<K, ODT>(w, x));
-      }
-    }
+    combine_chunk<K, DT, ODT, combine_shape(K).R, combine_shape(K).U>(rows, lo, hi, shift, w, out);
   }
 }
 
@@ -69,7 +59,7 @@ hipError_t launch_combine_t(const StreamArgs &a, const float *weights, void *out
   if (grid > cap) grid = cap;
   if (grid < 1) grid = 1;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), 0, s, rows, a.offsets,
-                     a.chunk_start, a.B, a.shift, a.vec ? 1 : 0, weights, out);
+                     a.chunk_start, a.B, a.shift, weights, out);
   return hipGetLastError();
 }
 

@@ -28,7 +28,7 @@ namespace {
 template <int K, int DT>
 __global__ __launch_bounds__(kThreads) void gram_partial_kernel(
     Rows<K> rows, const int64_t *__restrict__ offs, const int64_t *__restrict__ cs, int B,
-    int shift, int vec, double *__restrict__ partials) {
+    int shift, double *__restrict__ partials) {
   constexpr int64_t C = gram_chunk_elems(K, DT);
   constexpr int P = pairs(K);
   __shared__ double red[kThreads / kWave][P];
@@ -48,18 +48,9 @@ __global__ __launch_bounds__(kThreads) void gram_partial_kernel(
 #pragma unroll
     for (int p = 0; p < P; ++p) acc[p] = 0.0f;
 
-    if (vec) {
-      gram_chunk<K, DT>(rows, lo, hi, shift, acc);
-    } else {
-      for (int64_t n = lo + tid; n < hi; n += kThreads) {
-        float x[K];
-#pragma unroll
-        for (int i = 0; i < K; ++i) x[i] = load_elem<DT>(rows.p[i], n);
-        accumulate<K>(acc, x);
-      }
-    }
+    gram_chunk<K, DT>(rows, lo, hi, shift, acc);
 
-    // fixed-order reduction: then the 4 wavefronts in order
+    // fixed-order reduction; the 4 wavefronts in order
     reduce_lanes<P>(acc, red);
     __syncthreads();
     for (int p = tid; p < P; p += kThreads) {
@@ -122,7 +113,7 @@ hipError_t launch_gram_t(const StreamArgs &a, double *partials, hipStream_t s) {
   if (grid > cap) grid = cap;
   if (grid < 1) grid = 1;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), 0, s, rows, a.offsets,
-                     a.chunk_start, a.B, a.shift, a.vec ? 1 : 0, partials);
+                     a.chunk_start, a.B, a.shift, partials);
   return hipGetLastError();
 }
 

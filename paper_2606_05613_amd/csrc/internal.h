@@ -174,8 +174,8 @@ struct StreamArgs {
   const int64_t *chunk_start;  // device [B+1] (from the schedule kernel)
   const int64_t *group_start;  // device [B+1] finalize groups (Gram pass only)
   const uint32_t *err;         // device error word
-  int shift;                   // rows are 16-byte aligned at element n = shift (mod V)
-  bool vec;                    // 128-bit path allowed
+  int shift;                   // vectors start at elements n = shift (mod V): where the rows are 16-byte
+                               // aligned (Gram pass: row 0) and, in the combine, the output's stores
   int grid;                    // workgroups (0: automatic)
 };
 

@@ -53,7 +53,8 @@ struct Shared {
 };
 
 // MGDA: Frank-Wolfe on min_{a in simplex} a^T G a (Eq. shard-mgda), started
-// on the best pair of tasks, fixed iteration count.
+// on the best pair of tasks, fixed iteration count; a step that leaves the
+// point where it is ends it early (every later one would too: the same bits).
 template <typename Sync>
 __device__ void solve_mgda(Shared &S, int K, int iters, int t) {
   if (t == 0) {
@@ -95,6 +96,7 @@ __device__ void solve_mgda(Shared &S, int K, int iters, int t) {
     double aa = 0.0;
     for (int i = 0; i < K; ++i) aa += S.a[i] * S.v[i];
     const double g = pair_gamma(aa, S.v[ts], S.G[ts * K + ts]);
+    if (g == 1.0) break;  // the point stays, and with it every later step
     Sync()();
     if (t < K) {
       double na = g * S.a[t];
@@ -231,6 +233,7 @@ __device__ void solve_cagrad(Shared &S, int K, int iters, double c, int t) {
         gamma = g;
       }
     }
+    if (gamma == 0.0) break;  // the point stays, and with it every later step
     Sync()();
     if (t < K) {
       double na = (1.0 - gamma) * S.a[t];
@@ -240,189 +243,6 @@ __device__ void solve_cagrad(Shared &S, int K, int iters, double c, int t) {
     Sync()();
   }
   cagrad_primal<Sync>(S, K, r, invK, t);
-}
-
-// ---- register-only solvers for a compile-time K --------------------------
-// The same algorithms, operation for operation, as solve_mgda and
-// solve_cagrad above, with G and the iterate held in registers by every
-// lane (each lane computes the same scalars): no LDS round trips and no
-// synchronisation between steps.  Used where one bucket's solve sits on a
-// critical path.
-
-template <int K>
-__device__ __forceinline__ double pick(const double (&x)[K], int idx) {
-  double r = x[0];
-#pragma unroll
-  for (int i = 1; i < K; ++i) r = i == idx ? x[i] : r;
-  return r;
-}
-
-template <int K>
-__device__ void reg_solve_mgda(const double (&G)[K][K], int iters, double (&a)[K]) {
-  double best = 0.0, bg = 1.0;
-  int bi = 0, bj = 1;
-  bool first = true;
-#pragma unroll
-  for (int i = 0; i < K; ++i)
-#pragma unroll
-    for (int j = i + 1; j < K; ++j) {
-      const double aa = G[i][i], ab = G[i][j], bb = G[j][j];
-      const double g = pair_gamma(aa, ab, bb);
-      const double val = pair_value(g, aa, ab, bb);
-      if (first || val < best) {
-        first = false;
-        best = val;
-        bi = i;
-        bj = j;
-        bg = g;
-      }
-    }
-#pragma unroll
-  for (int i = 0; i < K; ++i) a[i] = i == bi ? bg : i == bj ? 1.0 - bg : 0.0;
-  for (int it = 0; it < iters; ++it) {
-    double v[K];
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      double s = 0.0;
-#pragma unroll
-      for (int j = 0; j < K; ++j) s += G[i][j] * a[j];
-      v[i] = s;
-    }
-    int ts = 0;
-    double m = v[0];
-#pragma unroll
-    for (int i = 1; i < K; ++i)
-      if (v[i] < m) {
-        m = v[i];
-        ts = i;
-      }
-    double aa = 0.0;
-#pragma unroll
-    for (int i = 0; i < K; ++i) aa += a[i] * v[i];
-    double gts = G[0][0];
-#pragma unroll
-    for (int i = 1; i < K; ++i) gts = i == ts ? G[i][i] : gts;
-    const double g = pair_gamma(aa, pick<K>(v, ts), gts);
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      double na = g * a[i];
-      if (i == ts) na += 1.0 - g;
-      a[i] = na;
-    }
-  }
-}
-
-template <int K>
-__device__ void reg_solve_cagrad(const double (&G)[K][K], int iters, double c, double (&wt)[K],
-                                 double (&w)[K]) {
-  const double invK = 1.0 / (double)K;
-  double b[K];
-#pragma unroll
-  for (int i = 0; i < K; ++i) {
-    double s = 0.0;
-#pragma unroll
-    for (int j = 0; j < K; ++j) s += G[i][j];
-    b[i] = s / (double)K;
-    w[i] = invK;
-  }
-  double tot = 0.0;
-#pragma unroll
-  for (int i = 0; i < K; ++i)
-#pragma unroll
-    for (int j = 0; j < K; ++j) tot += G[i][j];
-  double g0sq = tot / (double)(K * K);
-  g0sq = g0sq > 0.0 ? g0sq : 0.0;
-  const double r = c * sqrt(g0sq);
-  for (int it = 0; it < iters; ++it) {
-    double v[K];
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      double s = 0.0;
-#pragma unroll
-      for (int j = 0; j < K; ++j) s += G[i][j] * w[j];
-      v[i] = s;
-    }
-    double cq = 0.0, bw = 0.0;
-#pragma unroll
-    for (int i = 0; i < K; ++i) cq += w[i] * v[i];
-#pragma unroll
-    for (int i = 0; i < K; ++i) bw += b[i] * w[i];
-    const double nrm = sqrt(cq > 0.0 ? cq : 0.0);
-    int sidx = 0;
-    double m = 0.0;
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      const double gi = b[i] + (nrm > 1e-300 ? r * v[i] / nrm : 0.0);
-      if (i == 0 || gi < m) {
-        m = gi;
-        sidx = i;
-      }
-    }
-    double gss = G[0][0];
-#pragma unroll
-    for (int i = 1; i < K; ++i) gss = i == sidx ? G[i][i] : gss;
-    const double vs = pick<K>(v, sidx);
-    const double beta1 = pick<K>(b, sidx) - bw;
-    const double A = gss - 2.0 * vs + cq;
-    const double Bq = vs - cq;
-    // candidates in ascending order: 0, the interior stationary points
-    // (g1 <= g2 since A > 0), 1; the first of least F wins
-    double g1 = -1.0, g2 = -1.0;
-    const double D = r * r * A - beta1 * beta1;
-    if (A > 0.0 && D > 0.0) {
-      const double disc = (A * cq - Bq * Bq) / D;
-      if (disc >= 0.0) {
-        const double root = fabs(beta1) * sqrt(disc);
-        g1 = (-Bq - root) / A;
-        g2 = (-Bq + root) / A;
-      }
-    }
-    const bool h1 = g1 > 0.0 && g1 < 1.0, h2 = g2 > 0.0 && g2 < 1.0;
-    double gamma = 0.0, fbest = 0.0;
-    {
-      double q = A * 0.0 * 0.0 + 2.0 * Bq * 0.0 + cq;
-      q = q > 0.0 ? q : 0.0;
-      fbest = bw + beta1 * 0.0 + r * sqrt(q);
-    }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const bool has = k == 0 ? h1 : k == 1 ? h2 : true;
-      const double g = k == 0 ? g1 : k == 1 ? g2 : 1.0;
-      if (has) {
-        double q = A * g * g + 2.0 * Bq * g + cq;
-        q = q > 0.0 ? q : 0.0;
-        const double f = bw + beta1 * g + r * sqrt(q);
-        if (f < fbest) {
-          fbest = f;
-          gamma = g;
-        }
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      double na = (1.0 - gamma) * w[i];
-      if (i == sidx) na += gamma;
-      w[i] = na;
-    }
-  }
-  double v[K];
-#pragma unroll
-  for (int i = 0; i < K; ++i) {
-    double s = 0.0;
-#pragma unroll
-    for (int j = 0; j < K; ++j) s += G[i][j] * w[j];
-    v[i] = s;
-  }
-  double q = 0.0, dmax = 0.0;
-#pragma unroll
-  for (int i = 0; i < K; ++i) q += w[i] * v[i];
-#pragma unroll
-  for (int i = 0; i < K; ++i) dmax = G[i][i] > dmax ? G[i][i] : dmax;
-  const double nrm = sqrt(q > 0.0 ? q : 0.0);
-  const double scale = sqrt(dmax);
-  const bool degenerate = r == 0.0 || nrm <= 1e-12 * scale || nrm == 0.0;
-#pragma unroll
-  for (int i = 0; i < K; ++i) wt[i] = degenerate ? invK : invK + (r / nrm) * w[i];
 }
 
 // ---- lane-parallel solvers for a compile-time K <= 16 ---------------------
@@ -550,6 +370,7 @@ __device__ double lane_solve_mgda(const double *G, int iters, int lane) {
     const double git = task ? G[me * K + t] : 0.0;
     const double vt = lane_f64(v, t), gtt = lane_f64(gd, t);
     const double g = pair_gamma(aa, vt, gtt);
+    if (g == 1.0) break;  // the point stays, and with it every later step
     const double h = 1.0 - g;
     aa = g * g * aa + 2.0 * g * h * vt + h * h * gtt;
     v = g * v + h * git;
@@ -625,6 +446,7 @@ __device__ void lane_solve_cagrad(const double *G, int iters, double c, int lane
     argmin_step<kDppXor2>(fv, fi);
     const int win = __builtin_amdgcn_readlane(fi, 0);
     const double gamma = lane_f64(gc, win);
+    if (gamma == 0.0) break;  // the point stays, and with it every later step
     cq = lane_f64(qraw, win);
     v = (1.0 - gamma) * v + gamma * gis;
     bw = (1.0 - gamma) * bw + gamma * bs;

@@ -40,8 +40,11 @@ __device__ __forceinline__ void decode(const u32x4 &v, float *x) {
   }
 }
 
+// 16 bytes of a row at any element (gfx950 takes 128-bit global loads at any
+// byte address; a wavefront's load then touches one cache line more).
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
 __device__ __forceinline__ u32x4 stream_load(const void *base, int64_t vec_index) {
-  return __builtin_nontemporal_load(static_cast<const u32x4 *>(base) + vec_index);
+  return __builtin_nontemporal_load(static_cast<const u32x4_any *>(base) + vec_index);
 }
 
 // Raw buffer loads: address = descriptor base (scalar) + per-lane byte
@@ -95,8 +98,9 @@ __device__ __forceinline__ void my_chunks(int64_t total, int64_t &c0, int64_t &c
   c1 = c0 + per < total ? c0 + per : total;
 }
 
-// Split [lo, hi) into a scalar head, a run of whole 16-byte vectors starting
-// at an element index congruent to `shift` (mod V), and a scalar tail.
+// Split [lo, hi) into a scalar head, a run of whole vectors of V elements
+// starting at an element index congruent to `shift` (mod V), and a scalar
+// tail.
 template <int V>
 struct Split {
   int64_t lo_a;  // first vector element
