@@ -588,7 +588,7 @@ __global__ __launch_bounds__(kRefThreads, 2) void refill_kernel(Rows<K> rows, Re
     }
     return;
   }
-  if (a.err[1]) {
+  if (__builtin_expect(a.err[1] != 0u, 0)) {
     const TileArgs ta{a.offs, a.cs, a.B, a.shift, a.method, a.iters, a.c, a.order, a.gram, a.weights, a.aux, a.out,
                       a.partials, a.arrive, a.recs, a.err, a.spin_limit, a.nsolv};
     Td::run(rows, ta, lds.tiled);
