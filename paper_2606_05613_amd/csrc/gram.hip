@@ -4,8 +4,9 @@
 // PCGrad's local conflict test, Section 3.2) depend on the local gradients
 // only through these inner products, so this pass is the only one that
 // needs all K rows at once.  It is HBM-bound: K*N*s bytes read, K(K+1)
-// flops per element position, far below the fp32 vector ridge point, so
-// it uses plain fp32 FMAs and no matrix cores.
+// flops per element position, below the fp32 vector ridge point for fp32
+// rows and for few tasks: there it uses plain fp32 FMAs (bf16 rows of many
+// tasks: gram_mfma_kernel below).
 //
 // Design (gfx950): persistent workgroups of 4 wavefronts own contiguous
 // runs of chunks.  Every thread issues K*R independent 128-bit
@@ -63,6 +64,121 @@ __global__ __launch_bounds__(kThreads) void gram_partial_kernel(
   }
 }
 
+// The same partials of bf16 rows on the matrix cores, for kMfmaMinK tasks and
+// more.  There the FMA kernel is bound by issue, not by memory: at K = 16 an
+// element position costs 136 FMA and 16 conversions for 32 bytes, and its
+// accumulators leave one wavefront a SIMD.  Here a 16x16x32 product X X^T
+// takes 32 positions of 16 rows: lane l holds 16 bytes of row l % 16 (task l %
+// 16 % K of slice l % 16 / K: 16 / K runs of positions side by side, of which
+// the diagonal blocks count), the same register as left and as right operand,
+// so which positions a lane holds does not matter as long as all rows agree.
+// A wavefront reads a tile of 1 KiB of every row, lane after lane, and turns
+// it through LDS (its own part: no barrier), with the next tile's loads in
+// flight; read from memory in the operand's layout, 64 bytes of each row at a
+// time, it reached 2.5-4 TB/s.  The tile's rows lie kRowPitch apart, so that
+// eight lanes' 16-byte reads of eight rows fall on different banks.
+//
+// Products of bf16 are exact; an fp32 accumulator takes at most 256 of them
+// and is then added to an fp64 one.  2 GiB in ten buckets, us, FMA / matrix:
+// K=16 647 / 388, K=12 547 / 370, K=10 523 / 375, K=8 408 / 370, K=7 378 /
+// 355; K=6 374 / 373 and K=5 354 / 388, where the FMA kernel is bound by
+// memory.  Largest error relative to sqrt(G_ii G_jj) 1.5e-7 / 6e-9.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kMfmaMinK = 7;
+constexpr int kRowPitch = kWave + 1;  // 16-byte vectors
+
+template <int K>
+__global__ __launch_bounds__(kThreads) void gram_mfma_kernel(Rows<K> rows, const int64_t *__restrict__ offs,
+                                                             const int64_t *__restrict__ cs, int B, int shift,
+                                                             double *__restrict__ partials) {
+  constexpr int64_t C = gram_chunk_elems(K, BF16);
+  constexpr int P = pairs(K), V = vec_elems(BF16), S = 16 / K;
+  constexpr int kWaves = kThreads / kWave, kStep = 4 * S;  // vectors of a row in a product
+  constexpr int kSteps = kWave / kStep;                    // whole products in a tile (S = 3: 60 of 64 vectors)
+  constexpr int kTile = kSteps * kStep;                    // vectors of a row in a tile
+  __shared__ u32x4 tile[kWaves][K * kRowPitch];
+  __shared__ double red[2][kWaves * S][P];
+
+  int64_t c, cend;
+  my_chunks(cs[B], c, cend);
+  if (c >= cend) return;
+  int b = find_bucket(cs, B, c);
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int row = lane & 15, g = lane / 16, slice = row / K, task = row - slice * K;
+  const bool used = slice < S;
+  u32x4 *own = tile[wave];
+  const u32x4 *operand = own + (used ? task * kRowPitch + slice * 4 + g : 0);
+
+  for (int parity = 0; c < cend; ++c, parity ^= 1) {
+    while (cs[b + 1] <= c) ++b;
+    const int64_t lo = offs[b] + (c - cs[b]) * C;
+    const int64_t hi = lo + C < offs[b + 1] ? lo + C : offs[b + 1];
+    const Split<V> sp(lo, hi, shift);
+    double sum[4] = {0.0, 0.0, 0.0, 0.0};
+
+    if (wave == 0 && sp.nh + sp.nt > 0) {  // the scalar head (group 0) and tail (group 1) in one product
+      const uint16_t *mine = static_cast<const uint16_t *>(rows.p[0]);
+#pragma unroll
+      for (int i = 1; i < K; ++i) mine = task == i ? static_cast<const uint16_t *>(rows.p[i]) : mine;
+      const int64_t at = g == 0 ? lo : sp.hi_a;
+      const int n = slice == 0 ? (g == 0 ? sp.nh : g == 1 ? sp.nt : 0) : 0;
+      uint16_t x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = e < n ? mine[at + e] : (uint16_t)0;
+      const bf16x8 q = __builtin_bit_cast(bf16x8, x);
+      const f32x4 a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q, q, f32x4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sum[r] += (double)a[r];
+    }
+    u32x4 q[K];
+    const auto load = [&](int v0) {
+      const int v = v0 + lane;
+      const bool in = lane < kTile && v < sp.nv;
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        q[i] = u32x4{0u, 0u, 0u, 0u};
+        if (in) q[i] = stream_load(static_cast<const uint16_t *>(rows.p[i]) + sp.lo_a, v);
+      }
+    };
+    int v0 = wave * kTile;
+    if (v0 < sp.nv) load(v0);
+    for (; v0 < sp.nv; v0 += kWaves * kTile) {
+#pragma unroll
+      for (int i = 0; i < K; ++i) own[i * kRowPitch + lane] = q[i];
+      if (v0 + kWaves * kTile < sp.nv) load(v0 + kWaves * kTile);
+      // one wavefront's LDS accesses are executed in order: the compiler must
+      // only keep them so
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      f32x4 a[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
+#pragma unroll
+      for (int u = 0; u < kSteps; ++u) {
+        const bf16x8 x = __builtin_bit_cast(bf16x8, operand[u * kStep]);
+        a[u & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, x, a[u & 1], 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sum[r] += (double)a[0][r] + (double)a[1][r];
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    // lane l holds entries (g * 4 + r, l % 16); the diagonal blocks' upper
+    // triangles count
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = g * 4 + r - slice * K;
+      if (used && i >= 0 && i <= task) red[parity][wave * S + slice][i * K - i * (i - 1) / 2 + task - i] = sum[r];
+    }
+    __syncthreads();
+    if (tid < P) {
+      double s = red[parity][0][tid];
+#pragma unroll
+      for (int w = 1; w < kWaves * S; ++w) s += red[parity][w][tid];
+      partials[c * P + tid] = s;
+    }
+  }
+}
+
 // Finalize, level 1 (only where a bucket can have many chunks): one workgroup
 // per group of up to kFinalizeGroup consecutive chunks of one bucket
 // (grid-stride over the groups) leaves the group's sum in the slot of the
@@ -101,11 +217,18 @@ __global__ __launch_bounds__(kSumThreads) void gram_finalize_kernel(int K, const
   }
 }
 
+// Gram pass of one batch of buckets, by number of tasks and type.
+template <int K, int DT>
+constexpr auto gram_kernel() {
+  if constexpr (DT == BF16 && K >= kMfmaMinK) return gram_mfma_kernel<K>;
+  else return gram_partial_kernel<K, DT>;
+}
+
 template <int K, int DT>
 hipError_t launch_gram_t(const StreamArgs &a, double *partials, hipStream_t s) {
   Rows<K> rows;
   for (int i = 0; i < K; ++i) rows.p[i] = a.rows[i];
-  auto kern = gram_partial_kernel<K, DT>;
+  auto kern = gram_kernel<K, DT>();
   const int64_t C = gram_chunk_elems(K, DT);
   const int64_t cap = (a.N + C - 1) / C + a.B;
   static const int occ = occupancy(kern);
