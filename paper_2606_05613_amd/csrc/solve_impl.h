@@ -296,18 +296,26 @@ __device__ __forceinline__ void argmin_step(double &v, int &idx) {
   v = take ? ov : v;
   idx = take ? oi : idx;
 }
-// Lowest index among the least v over lanes 0..K-1 (v must be +inf and idx
-// above K on lanes K..15), broadcast.
+template <int CTRL>
+__device__ __forceinline__ double min_step(double v) {
+  const double o = dpp_f64<CTRL>(v);
+  return o < v ? o : v;
+}
+// Lowest index among the least v over lanes 0..K-1 (v must be +inf on lanes
+// K..15), broadcast.  The least value first, then the lowest lane that holds
+// it: 40 steps of MGDA at K = 10, 6,564 buckets, 51 us, against 58 with the
+// index carried through the butterfly (argmin_step); at K <= 4 alike.
 template <int K>
-__device__ __forceinline__ int row_argmin(double v, int idx) {
+__device__ __forceinline__ int row_argmin(double v) {
   static_assert(K <= 16, "one row of lanes");
-  argmin_step<kDppXor1>(v, idx);
-  argmin_step<kDppXor2>(v, idx);
+  double m = min_step<kDppXor1>(v);
+  m = min_step<kDppXor2>(m);
   if constexpr (K > 4) {
-    argmin_step<kDppRor4>(v, idx);
-    argmin_step<kDppRor8>(v, idx);
+    m = min_step<kDppRor4>(m);
+    m = min_step<kDppRor8>(m);
   }
-  return __builtin_amdgcn_readlane(idx, 0);
+  const uint64_t at = __ballot(v == lane_f64(m, 0)) & ((1u << K) - 1u);
+  return at ? __builtin_ctzll(at) : 0;
 }
 
 // First pair (i < j, lexicographic) of least two-point norm and its step:
@@ -366,7 +374,7 @@ __device__ double lane_solve_mgda(const double *G, int iters, int lane) {
   for (int j = 0; j < K; ++j) v += gi[j] * (j == bi ? bg : j == bj ? 1.0 - bg : 0.0);
   double aa = row_sum<K>(task ? own * v : 0.0);  // a^T G a
   for (int it = 0; it < iters; ++it) {
-    const int t = row_argmin<K>(task ? v : __builtin_inf(), task ? lane : kWave);
+    const int t = row_argmin<K>(task ? v : __builtin_inf());
     const double git = task ? G[me * K + t] : 0.0;
     const double vt = lane_f64(v, t), gtt = lane_f64(gd, t);
     const double g = pair_gamma(aa, vt, gtt);
@@ -412,10 +420,10 @@ __device__ void lane_solve_cagrad(const double *G, int iters, double c, int lane
   for (int j = 0; j < K; ++j) v += gi[j] * invK;
   double cq = row_sum<K>(task ? own * v : 0.0);   // w^T G w
   double bw = row_sum<K>(task ? bo * own : 0.0);  // b^T w
+  double nrm = sqrt(cq > 0.0 ? cq : 0.0);
   for (int it = 0; it < iters; ++it) {
-    const double nrm = sqrt(cq > 0.0 ? cq : 0.0);
     const double grad = bo + (nrm > 1e-300 ? r * v / nrm : 0.0);
-    const int s = row_argmin<K>(task ? grad : __builtin_inf(), task ? lane : kWave);
+    const int s = row_argmin<K>(task ? grad : __builtin_inf());
     const double gis = task ? G[me * K + s] : 0.0;
     const double vs = lane_f64(v, s);
     const double bs = lane_f64(bo, s);
@@ -439,15 +447,13 @@ __device__ void lane_solve_cagrad(const double *G, int iters, double c, int lane
     const bool valid = lane < 4 && (q4 == 0 || q4 == 3 || (gc > 0.0 && gc < 1.0));
     const double qraw = A * gc * gc + 2.0 * Bq * gc + cq;
     const double qq = qraw > 0.0 ? qraw : 0.0;
-    const double f = valid ? bw + beta1 * gc + r * sqrt(qq) : __builtin_inf();
-    double fv = f;
-    int fi = valid ? q4 : kWave;
-    argmin_step<kDppXor1>(fv, fi);
-    argmin_step<kDppXor2>(fv, fi);
-    const int win = __builtin_amdgcn_readlane(fi, 0);
+    const double root_q = sqrt(qq);
+    const double f = valid ? bw + beta1 * gc + r * root_q : __builtin_inf();
+    const int win = row_argmin<4>(f);
     const double gamma = lane_f64(gc, win);
     if (gamma == 0.0) break;  // the point stays, and with it every later step
     cq = lane_f64(qraw, win);
+    nrm = lane_f64(root_q, win);  // the square root of cq, or of 0 where that is negative
     v = (1.0 - gamma) * v + gamma * gis;
     bw = (1.0 - gamma) * bw + gamma * bs;
     double no = (1.0 - gamma) * own;
@@ -461,7 +467,7 @@ __device__ void lane_solve_cagrad(const double *G, int iters, double c, int lane
     const double x = lane_f64(gd, l);
     dmax = x > dmax ? x : dmax;
   }
-  const double nrm = sqrt(q > 0.0 ? q : 0.0);
+  nrm = sqrt(q > 0.0 ? q : 0.0);
   const double scale = sqrt(dmax);
   const bool degenerate = r == 0.0 || nrm <= 1e-12 * scale || nrm == 0.0;
   *wt = degenerate ? invK : invK + (r / nrm) * own;
