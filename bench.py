@@ -64,8 +64,8 @@ def log(msg):
 # The sources each timed kernel is compiled from (its file and the headers it
 # includes): a committed counter summary applies while these are unchanged.
 KERNEL_SOURCES = {
-    "gram": ["gram.hip", "chunk.h", "gram_sum.h", "combine_impl.h", "stream_common.h", "internal.h"],
-    "combine": ["combine.hip", "chunk.h", "combine_impl.h", "stream_common.h", "internal.h"],
+    "gram": ["gram.hip", "chunk.h", "gram_sum.h", "schedule.h", "combine_impl.h", "stream_common.h", "internal.h"],
+    "combine": ["combine.hip", "chunk.h", "schedule.h", "combine_impl.h", "stream_common.h", "internal.h"],
     "hybrid": ["hybrid.hip", "coop_common.h", "combine_impl.h", "solve_impl.h", "stream_common.h",
                "internal.h"],
     "refill": ["refill.hip", "refill.h", "tiled.h", "chunk.h", "coop_common.h", "combine_impl.h", "solve_impl.h",

@@ -9,6 +9,7 @@
 #include "bkmoo.h"
 #include "internal.h"
 #include "refill.h"
+#include "schedule.h"
 
 namespace bkmoo {
 
@@ -111,6 +112,15 @@ bkmoo_status check_hparams(int method, const bkmoo_hparams *hp) {
 
 // K beyond what the method supports (exact solvers enumerate 2^K - 1 supports).
 bool k_unsupported(int K, int method) { return K > kMaxK || (is_exact(method) && K > kExactMaxK); }
+
+// The schedule kernel before a streaming pass of many buckets; with few the
+// pass makes its schedule itself (own_schedule).
+hipError_t schedule_pass(const int64_t *offsets, int B, int64_t N, int K, int dt, int64_t *chunk_start,
+                         int64_t *group_start, uint32_t *err, hipStream_t s) {
+  if (B <= kSelfBuckets) return hipSuccess;
+  return launch_schedule(offsets, B, N, gram_chunk_elems(K, dt), chunk_start, group_start, err, nullptr, 0,
+                         PipePlan{}, s);
+}
 
 bkmoo_status hip_status(hipError_t e) { return e == hipSuccess ? BKMOO_OK : BKMOO_EHIP; }
 
@@ -439,10 +449,9 @@ bkmoo_status bkmoo_gram(int32_t K, const void *const *grads, bkmoo_dtype dt, int
   const Layout L = layout(K, N, B, dt);
   if (ws_bytes < L.total) return BKMOO_EWORKSPACE;
   const Carved w = carve(workspace, L);
-  hipError_t e = launch_schedule(bucket_offsets, B, N, gram_chunk_elems(K, dt), w.chunk_start,
-                                 w.group_start, w.err, nullptr, 0, PipePlan{}, stream);
-  if (e != hipSuccess) return BKMOO_EHIP;
-  const StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, w.group_start, w.err,
+  if (schedule_pass(bucket_offsets, B, N, K, (int)dt, w.chunk_start, w.group_start, w.err, stream) != hipSuccess)
+    return BKMOO_EHIP;
+  const StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, w.group_start, w.err, B > kSelfBuckets,
                      shift, g_grid_override.load()};
   if (launch_gram_partials(a, w.partials, stream) != hipSuccess) return BKMOO_EHIP;
   return hip_status(launch_gram_finalize(a, w.partials, gram, stream));
@@ -476,11 +485,10 @@ bkmoo_status bkmoo_combine(int32_t K, const void *const *grads, bkmoo_dtype dt, 
   const Layout L = layout(K, N, B, dt);
   if (ws_bytes < L.total) return BKMOO_EWORKSPACE;
   const Carved w = carve(workspace, L);
-  hipError_t e = launch_schedule(bucket_offsets, B, N, gram_chunk_elems(K, dt), w.chunk_start,
-                                 nullptr, w.err, nullptr, 0, PipePlan{}, stream);
-  if (e != hipSuccess) return BKMOO_EHIP;
-  const StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, nullptr, w.err, out_shift,
-                     g_grid_override.load()};
+  if (schedule_pass(bucket_offsets, B, N, K, (int)dt, w.chunk_start, nullptr, w.err, stream) != hipSuccess)
+    return BKMOO_EHIP;
+  const StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, nullptr, w.err, B > kSelfBuckets,
+                     out_shift, g_grid_override.load()};
   return hip_status(launch_combine(a, weights, out, (int)out_dt, stream));
 }
 
@@ -556,10 +564,9 @@ bkmoo_status resolve_impl(int32_t K, const void *const *grads, bkmoo_dtype dt, i
     return hip_status(e);
   }
 
-  hipError_t e = launch_schedule(bucket_offsets, B, N, gram_chunk_elems(K, dt), w.chunk_start,
-                                 w.group_start, w.err, nullptr, 0, PipePlan{}, stream);
+  hipError_t e = schedule_pass(bucket_offsets, B, N, K, (int)dt, w.chunk_start, w.group_start, w.err, stream);
   if (e != hipSuccess) return BKMOO_EHIP;
-  StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, w.group_start, w.err, shift,
+  StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, w.group_start, w.err, B > kSelfBuckets, shift,
                g_grid_override.load()};
   if (launch_gram_partials(a, w.partials, stream) != hipSuccess) return BKMOO_EHIP;
   if (is_exact(method)) {
@@ -570,6 +577,7 @@ bkmoo_status resolve_impl(int32_t K, const void *const *grads, bkmoo_dtype dt, i
   }
   if (e != hipSuccess) return BKMOO_EHIP;
   a.shift = out_shift;
+  a.scheduled = true;  // by the Gram pass
   return hip_status(launch_combine(a, W, out, (int)out_dt, stream));
 }
 

@@ -21,17 +21,23 @@
 // to odd into a format with at least two more significand bits than the
 // target makes the second rounding the correct single rounding.
 #include "chunk.h"
+#include "schedule.h"
 
 namespace bkmoo {
 
 namespace {
 
-template <int K, int DT, int ODT>
+template <int K, int DT, int ODT, bool SELF>
 __global__ __launch_bounds__(kThreads) void combine_kernel(
-    Rows<K> rows, const int64_t *__restrict__ offs, const int64_t *__restrict__ cs, int B,
-    int shift, const float *__restrict__ weights, void *out) {
+    Rows<K> rows, const int64_t *__restrict__ offs, const int64_t *__restrict__ gcs, int B,
+    int shift, ScheduleOut sched, const float *__restrict__ weights, void *out) {
   constexpr int64_t C = combine_chunk_elems(K, DT);
 
+  __shared__ int64_t lcs[SELF ? kSelfBuckets + 1 : 1];
+  if constexpr (SELF) {
+    if (!own_schedule(offs, B, C * kCombineParts, sched, lcs)) return;
+  }
+  const int64_t *cs = SELF ? lcs : gcs;
   const int64_t total = cs[B] * kCombineParts;
 
   for (int64_t c = blockIdx.x; c < total; c += gridDim.x) {
@@ -47,20 +53,26 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(
   }
 }
 
-template <int K, int DT, int ODT>
-hipError_t launch_combine_t(const StreamArgs &a, const float *weights, void *out, hipStream_t s) {
+template <int K, int DT, int ODT, bool SELF>
+hipError_t launch_combine_s(const StreamArgs &a, const float *weights, void *out, hipStream_t s) {
   Rows<K> rows;
   for (int i = 0; i < K; ++i) rows.p[i] = a.rows[i];
-  auto kern = combine_kernel<K, DT, ODT>;
+  auto kern = combine_kernel<K, DT, ODT, SELF>;
   const int64_t C = combine_chunk_elems(K, DT);
   const int64_t cap = (a.N + C - 1) / C + a.B;
   static const int occ = occupancy(kern);
-  int64_t grid = a.grid > 0 ? a.grid : (int64_t)device_cu_count() * occ;
+  int64_t grid = a.grid > 0 ? a.grid : stream_grid(K, combine_shape(K).R, occ, cap);
   if (grid > cap) grid = cap;
   if (grid < 1) grid = 1;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), 0, s, rows, a.offsets,
-                     a.chunk_start, a.B, a.shift, weights, out);
+                     a.chunk_start, a.B, a.shift, ScheduleOut{a.N, a.chunk_start, nullptr, a.err}, weights, out);
   return hipGetLastError();
+}
+
+template <int K, int DT, int ODT>
+hipError_t launch_combine_t(const StreamArgs &a, const float *weights, void *out, hipStream_t s) {
+  return a.scheduled ? launch_combine_s<K, DT, ODT, false>(a, weights, out, s)
+                     : launch_combine_s<K, DT, ODT, true>(a, weights, out, s);
 }
 
 template <int DT, int ODT>

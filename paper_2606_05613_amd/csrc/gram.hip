@@ -21,19 +21,25 @@
 // the result is bitwise independent of the grid and of scheduling.
 #include "chunk.h"
 #include "gram_sum.h"
+#include "schedule.h"
 
 namespace bkmoo {
 
 namespace {
 
-template <int K, int DT>
+template <int K, int DT, bool SELF>
 __global__ __launch_bounds__(kThreads) void gram_partial_kernel(
-    Rows<K> rows, const int64_t *__restrict__ offs, const int64_t *__restrict__ cs, int B,
-    int shift, double *__restrict__ partials) {
+    Rows<K> rows, const int64_t *__restrict__ offs, const int64_t *__restrict__ gcs, int B,
+    int shift, ScheduleOut sched, double *__restrict__ partials) {
   constexpr int64_t C = gram_chunk_elems(K, DT);
   constexpr int P = pairs(K);
   __shared__ double red[kThreads / kWave][P];
 
+  __shared__ int64_t lcs[SELF ? kSelfBuckets + 1 : 1];
+  if constexpr (SELF) {
+    if (!own_schedule(offs, B, C, sched, lcs)) return;
+  }
+  const int64_t *cs = SELF ? lcs : gcs;
   int64_t c, cend;
   my_chunks(cs[B], c, cend);
   if (c >= cend) return;
@@ -88,10 +94,10 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kMfmaMinK = 7;
 constexpr int kRowPitch = kWave + 1;  // 16-byte vectors
 
-template <int K>
+template <int K, bool SELF>
 __global__ __launch_bounds__(kThreads) void gram_mfma_kernel(Rows<K> rows, const int64_t *__restrict__ offs,
-                                                             const int64_t *__restrict__ cs, int B, int shift,
-                                                             double *__restrict__ partials) {
+                                                             const int64_t *__restrict__ gcs, int B, int shift,
+                                                             ScheduleOut sched, double *__restrict__ partials) {
   constexpr int64_t C = gram_chunk_elems(K, BF16);
   constexpr int P = pairs(K), V = vec_elems(BF16), S = 16 / K;
   constexpr int kWaves = kThreads / kWave, kStep = 4 * S;  // vectors of a row in a product
@@ -100,6 +106,11 @@ __global__ __launch_bounds__(kThreads) void gram_mfma_kernel(Rows<K> rows, const
   __shared__ u32x4 tile[kWaves][K * kRowPitch];
   __shared__ double red[2][kWaves * S][P];
 
+  __shared__ int64_t lcs[SELF ? kSelfBuckets + 1 : 1];
+  if constexpr (SELF) {
+    if (!own_schedule(offs, B, C, sched, lcs)) return;
+  }
+  const int64_t *cs = SELF ? lcs : gcs;
   int64_t c, cend;
   my_chunks(cs[B], c, cend);
   if (c >= cend) return;
@@ -218,26 +229,31 @@ __global__ __launch_bounds__(kSumThreads) void gram_finalize_kernel(int K, const
 }
 
 // Gram pass of one batch of buckets, by number of tasks and type.
-template <int K, int DT>
+template <int K, int DT, bool SELF>
 constexpr auto gram_kernel() {
-  if constexpr (DT == BF16 && K >= kMfmaMinK) return gram_mfma_kernel<K>;
-  else return gram_partial_kernel<K, DT>;
+  if constexpr (DT == BF16 && K >= kMfmaMinK) return gram_mfma_kernel<K, SELF>;
+  else return gram_partial_kernel<K, DT, SELF>;
+}
+
+template <int K, int DT, bool SELF>
+hipError_t launch_gram_s(const StreamArgs &a, double *partials, hipStream_t s) {
+  Rows<K> rows;
+  for (int i = 0; i < K; ++i) rows.p[i] = a.rows[i];
+  auto kern = gram_kernel<K, DT, SELF>();
+  const int64_t C = gram_chunk_elems(K, DT);
+  const int64_t cap = (a.N + C - 1) / C + a.B;
+  static const int occ = occupancy(kern);
+  int64_t grid = a.grid > 0 ? a.grid : stream_grid(K, gram_shape(K).R, occ, cap);
+  if (grid > cap) grid = cap;
+  if (grid < 1) grid = 1;
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), 0, s, rows, a.offsets,
+                     a.chunk_start, a.B, a.shift, ScheduleOut{a.N, a.chunk_start, a.group_start, a.err}, partials);
+  return hipGetLastError();
 }
 
 template <int K, int DT>
 hipError_t launch_gram_t(const StreamArgs &a, double *partials, hipStream_t s) {
-  Rows<K> rows;
-  for (int i = 0; i < K; ++i) rows.p[i] = a.rows[i];
-  auto kern = gram_kernel<K, DT>();
-  const int64_t C = gram_chunk_elems(K, DT);
-  const int64_t cap = (a.N + C - 1) / C + a.B;
-  static const int occ = occupancy(kern);
-  int64_t grid = a.grid > 0 ? a.grid : (int64_t)device_cu_count() * occ;
-  if (grid > cap) grid = cap;
-  if (grid < 1) grid = 1;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), 0, s, rows, a.offsets,
-                     a.chunk_start, a.B, a.shift, partials);
-  return hipGetLastError();
+  return a.scheduled ? launch_gram_s<K, DT, false>(a, partials, s) : launch_gram_s<K, DT, true>(a, partials, s);
 }
 
 template <int DT>

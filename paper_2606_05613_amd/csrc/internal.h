@@ -171,9 +171,10 @@ struct StreamArgs {
   int64_t N;
   int B;
   const int64_t *offsets;      // device [B+1]
-  const int64_t *chunk_start;  // device [B+1] (from the schedule kernel)
-  const int64_t *group_start;  // device [B+1] finalize groups (Gram pass only)
-  const uint32_t *err;         // device error word
+  int64_t *chunk_start;        // device [B+1]
+  int64_t *group_start;        // device [B+1] finalize groups (Gram pass only)
+  uint32_t *err;               // device error word
+  bool scheduled;              // these three are there (else the pass makes them, B <= kSelfBuckets)
   int shift;                   // vectors start at elements n = shift (mod V): where the rows are 16-byte
                                // aligned (Gram pass: row 0) and, in the combine, the output's stores
   int grid;                    // workgroups (0: automatic)
@@ -276,6 +277,28 @@ hipError_t launch_hybrid(int K, int dt, int out_dt, const void *const *rows, con
                          const HybLayout &layout, hipStream_t s);
 
 int device_cu_count();
+
+// Workgroups of a streaming pass of `cap` chunks at most.  A long pass is
+// fastest with no more wavefronts than keep about 128 KiB of loads in flight
+// on a CU (a workgroup has 8 KiB per task and vector of a step, two steps at a
+// time): further ones only spread the accesses over more of memory.  2 GiB
+// read, Gram / combine, us, as many as fit (4-6 a CU) against two a CU: K=4
+// fp32 371 / 569 -> 350 / 529, K=8 fp32 403 / 516 -> 365 / 496, K=10 fp32 377 /
+// 491 -> 357 / 460, K=4 bf16 374 / 558 -> 357 / 552; K=2 bf16 374 / 705 -> 340
+// / 675 with four, 432 / 782 with two.  A short pass (fewer than kLongPass
+// chunks for each of them) takes all that fit.
+constexpr int kLongPass = 4;
+constexpr int stream_wgs(int K, int R) {
+  const int n = (16 + K * R / 2) / (K * R);
+  return n < 2 ? 2 : n;
+}
+inline int64_t stream_grid(int K, int R, int occ, int64_t cap) {
+  const int64_t cus = device_cu_count(), few = cus * stream_wgs(K, R);
+  int64_t grid = cus * occ;
+  if (grid > few && cap >= kLongPass * few) grid = few;
+  if (grid > cap) grid = cap;
+  return grid < 1 ? 1 : grid;
+}
 
 // Resident workgroups of kThreads per CU for a kernel (at least 1).
 template <typename Kern>

@@ -91,7 +91,9 @@ __device__ __forceinline__ int find_bucket(const int64_t *__restrict__ cs, int B
   return lo;
 }
 
-// The contiguous range of chunks workgroup `blockIdx.x` owns.
+// The contiguous range of chunks workgroup `blockIdx.x` owns.  Equal ranges,
+// the last workgroups without any, beat ranges that differ by one chunk (K=16
+// bf16, 1,900 chunks on 512 workgroups, 307 against 315 us a call).
 __device__ __forceinline__ void my_chunks(int64_t total, int64_t &c0, int64_t &c1) {
   const int64_t per = (total + gridDim.x - 1) / gridDim.x;
   c0 = (int64_t)blockIdx.x * per;
