@@ -1,6 +1,7 @@
 """The Gram finalize at the line where chunk slots are first added in groups
-(512 chunks in a call), and the resolve call's finalize that also solves,
-against float64 sums of the same bytes."""
+(512 chunks in a call), the resolve call's finalize that also solves, and the
+schedule that a streaming pass makes for itself, against float64 sums of the
+same bytes."""
 
 import numpy as np
 import pytest
@@ -52,3 +53,41 @@ def test_grouped_and_direct_sums(gpu_lib, K, dtype, past):
     assert torch.equal(G, G2)
     w, _ = oracle.solve(G.cpu().numpy(), method, 20)
     assert_weights(W.cpu().numpy().astype(np.float64), w, "weights(iso)", f"K={K} past={past}")
+
+
+@pytest.mark.parametrize("B", [1, 256, 257, 511, 512, 1025])
+@pytest.mark.parametrize("K,dtype", [(2, "f32"), (8, "bf16")])
+def test_schedule_by_the_pass_or_its_own_kernel(gpu_lib, K, dtype, B):
+    """Bucket counts at the edges of a workgroup's scan and of the line (511)
+    up to which a streaming pass makes its own schedule; also with offsets
+    that it has to reject."""
+    rng = np.random.default_rng(B)
+    lens = rng.integers(0, 3_000, size=B)
+    lens[B // 2] += 40_000
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    n = int(offs[-1])
+    print(f"case schedule K={K} {dtype} B={B} N={n}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(B)
+    x = torch.randn((K, n), generator=gen, device="cuda").to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    o = torch.from_numpy(offs).cuda()
+    ws = torch.empty(gpu_lib.workspace_size(K, n, B, x.dtype), dtype=torch.uint8, device="cuda")
+    G = gpu_lib.gram(x, o, workspace=ws)
+    assert_gram(G.cpu().numpy(), _gram64(x, offs), dtype, f"B={B}")
+    w = torch.randn((B, K), generator=gen, device="cuda")
+    out = gpu_lib.combine(x, o, w, out_dtype=torch.float32, workspace=ws)
+    per = torch.repeat_interleave(torch.arange(B, device="cuda"), torch.from_numpy(lens).cuda())
+    want = (w.double()[per].t() * x.double()).sum(0)
+    scale = (w.double()[per].t() * x.double()).abs().sum(0)
+    # an fp32 FMA chain of K terms
+    assert bool(((out.double() - want).abs() <= K * 2.0 ** -24 * scale + 1e-30).all())
+    if B > 2:
+        bad = o.clone()
+        bad[1] = bad[2] + 1
+        keep = torch.full((n,), 7.0, device="cuda")
+        gpu_lib.combine(x, bad, w, out=keep, workspace=ws)
+        assert gpu_lib.read_device_error(ws) == gpu_lib.DEVERR_OFFSETS and bool((keep == 7.0).all())
+        assert bool(torch.isnan(gpu_lib.gram(x, bad, workspace=ws)).all())
+        assert gpu_lib.read_device_error(ws) == gpu_lib.DEVERR_OFFSETS
+        gpu_lib.gram(x, o, workspace=ws)
+        assert gpu_lib.read_device_error(ws) == 0
