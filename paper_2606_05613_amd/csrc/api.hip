@@ -325,6 +325,19 @@ constexpr double kRefillMinRoundMiB = 64.0, kRefillMiBPerUs = 2.0;
 // CAGrad 5.49 / 5.04: at K = 3 the refill kernel wins for every method.
 constexpr double kRefillOverHybridUs = 4.0;
 
+// Gradients that the last-level cache holds are read a second time from there,
+// and three ordinary launches have no gaps of ~10 us around them as a
+// cooperative one has: with many tasks, of which the refill kernel keeps the
+// smaller share on chip, the two passes win there.  13 / 31 buckets, inputs
+// new to the caches, us, refill / two passes: K=8 bf16 PCGrad 90 MiB 71 / 52,
+// 130 MiB 86 / 74 and 84 / 80, 200 MiB 124 / 95, 300 MiB 144 / 141 and 140 / 141, 450 MiB 183 /
+// 201 and 192 / 195 (MGDA alike); K=10 fp32 MGDA 130 MiB 86 / 69, 200 MiB 119 /
+// 116, 300 MiB 147 / 139 and 133 / 139.  With fewer tasks there is no such
+// line: K=4 bf16 65 / 55, 78 / 78, 121 / 102, K=4 fp32 75 / 85 and 103 / 109,
+// K=3 83 / 88 and 129 / 114, K=2 fp32 58 / 63 and 74 / 79 at 90 to 200 MiB.
+constexpr int kSmallMinK = 7;
+constexpr double kSmallMiB = 256.0;
+
 int refill_groups(int K, int dt, int64_t N, int B) {
   const double bucket_mib = (double)N / B * K * elem_bytes(dt) / (1 << 20);
   int g = (int)(kRefillRoundMiB / (bucket_mib > 1e-9 ? bucket_mib : 1e-9) + 0.5);
@@ -348,6 +361,7 @@ int choose_refill(int K, int dt, int out_dt, int64_t N, int B, bool vec, int met
     return 0;
   if (mode == BKMOO_PATH_REFILL) return g;
   if (B < kHybridMinBuckets) return 0;
+  if (K >= kSmallMinK && (double)N * K * elem_bytes(dt) <= kSmallMiB * (1 << 20)) return 0;
   const double round_mib = (double)N / B * K * elem_bytes(dt) / (1 << 20) * groups;
   const double min_mib = kRefillMinRoundMiB + kRefillMiBPerUs * solve_latency_us(method, K, iters);
   return round_mib >= min_mib && (round_mib <= kRefillMaxRoundMiB || groups == 1) ? g : 0;

@@ -152,3 +152,14 @@ def test_forced_hybrid_and_unknown_paths(gpu_lib, rows_4x2g):
     for bad in (-1, 2, 5):
         with pytest.raises(gpu_lib.BkmooError):
             gpu_lib.set_resolve_path(bad)
+
+
+@pytest.mark.parametrize("K,mib,want", [(8, 104, "two-pass"), (8, 250, "two-pass"), (8, 264, "refill"),
+                                        (7, 104, "two-pass"), (6, 104, "refill"), (10, 200, "two-pass")])
+def test_small_calls_of_many_tasks_take_the_two_passes(gpu_lib, K, mib, want):
+    """Seven tasks and more, at most 256 MiB of gradients in all (13 buckets):
+    the two passes; beyond, or with fewer tasks, the refill kernel."""
+    names = {gpu_lib.PATH_TWO_PASS: "two-pass", gpu_lib.PATH_HYBRID: "hybrid", gpu_lib.PATH_REFILL: "refill"}
+    g = torch.empty((K, (mib * MIB // (2 * K)) // 8 * 8), dtype=torch.bfloat16, device="cuda")
+    gpu_lib.set_resolve_path(0)
+    assert names[gpu_lib.resolve_path(g, 14, "pcgrad", 0)] == want
