@@ -335,8 +335,8 @@ bkmoo_status bkmoo_gram_reduce(int32_t K, int32_t B, int32_t T, const double *pa
  * cosine similarity) is negative (Section 2.1; the appendix definition of
  * conflicting gradients); Figure 1 follows the mean and standard deviation
  * of the pairwise cosines and counts a step as conflicting when some pair
- * is negative.  Reads only `gram` (B*K*K*8 bytes), one thread per bucket,
- * fp64, pairs i < j in lexicographic order.
+ * is negative.  Reads only `gram` (B*K*K*8 bytes), a few lanes per bucket
+ * (as many as it has pairs), fp64, sums in a fixed order.
  *
  *   gram     (in)  fp64 [B][K][K] (as written by bkmoo_gram / bkmoo_resolve)
  *   cosines  (out, may be NULL) fp64 [B][K][K], symmetric:

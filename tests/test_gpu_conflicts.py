@@ -85,3 +85,35 @@ def test_conflicts_end_to_end(gpu_lib, K, dtype):
     want = oracle.conflicts(oracle.gram(oracle.decode_rows(rows), wl.offsets()))
     tau = TAU[dtype]
     assert_conflicts(got, want, wl.name, tol_cos=3 * tau, tol_sum=3 * tau, sign_margin=3 * tau)
+
+
+def _median_us(call, reps=20, rounds=7):
+    start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    call()
+    took = []
+    for _ in range(rounds):
+        start.record()
+        for _ in range(reps):
+            call()
+        end.record()
+        end.synchronize()
+        took.append(start.elapsed_time(end) / reps * 1e3)
+    return sorted(took)[rounds // 2]
+
+
+@pytest.mark.parametrize("K,many,factor", [(2, 400_000, 5), (4, 400_000, 7)])
+def test_conflicts_of_many_buckets_of_few_tasks(gpu_lib, K, many, factor):
+    """A bucket takes no more lanes than it has pairs, and its bits do not
+    depend on how many: forty times the buckets, at most 2.4 times the time of
+    a call (11 us from Python); with a wavefront a bucket it is 18 times."""
+    G = torch.from_numpy(_grams_with_edges(K, 1000, 3 + K)).cuda()
+    few, lots = G.repeat(10, 1, 1).contiguous(), G.repeat(many // 1000, 1, 1).contiguous()
+    print(f"case conflicts K={K} B={many}", flush=True)
+    short, full = gpu_lib.conflicts(few), gpu_lib.conflicts(lots)
+    bits = lambda t: t.view(torch.int64) if t.dtype == torch.float64 else t
+    for a, b in zip(short, full):
+        assert torch.equal(bits(a), bits(b[: len(a)])) and torch.equal(bits(a), bits(b[-len(a):]))
+    quick = _median_us(lambda: gpu_lib.conflicts(few, cosines=False))
+    slow = _median_us(lambda: gpu_lib.conflicts(lots, cosines=False))
+    print(f"10,000 buckets {quick:.1f} us, {many} {slow:.1f} us", flush=True)
+    assert slow <= factor * quick
