@@ -15,8 +15,8 @@
 // a fixed xor butterfly across the wavefront, then in fp64 across the 4
 // wavefronts through LDS in wave order, and land in a per-chunk slot.  The
 // finalize adds a bucket's chunk slots in fp64 in an order fixed by the
-// bucket's chunk count and N (where a bucket can have many chunks, groups of
-// consecutive chunks first, then the groups); a resolve call adds them in
+// bucket's chunk count (in a bucket of many chunks groups of consecutive
+// chunks first, then the groups); a resolve call adds them in
 // the kernel that also solves the bucket's problem (solve.hip).  No atomics:
 // the result is bitwise independent of the grid and of scheduling.
 #include "chunk.h"
@@ -190,7 +190,7 @@ __global__ __launch_bounds__(kThreads) void gram_mfma_kernel(Rows<K> rows, const
   }
 }
 
-// Finalize, level 1 (only where a bucket can have many chunks): one workgroup
+// Finalize, level 1 (only buckets of kSumDirect chunks and more): one workgroup
 // per group of up to kFinalizeGroup consecutive chunks of one bucket
 // (grid-stride over the groups) leaves the group's sum in the slot of the
 // group's first chunk, which only this workgroup reads.
@@ -207,18 +207,17 @@ __global__ __launch_bounds__(kSumThreads) void gram_group_kernel(int P, int B, c
   }
 }
 
-// Finalize, level 2: one workgroup per bucket adds the bucket's chunk slots
-// (step 1) or group sums (step kFinalizeGroup) and writes the symmetric
-// K x K matrix (NaN everywhere when the offsets were rejected by the
-// schedule).
-__global__ __launch_bounds__(kSumThreads) void gram_finalize_kernel(int K, const int64_t *__restrict__ cs, int step,
+// Finalize, level 2: one workgroup per bucket adds the bucket's chunk slots or
+// group sums and writes the symmetric K x K matrix (NaN everywhere when the
+// offsets were rejected by the schedule).
+__global__ __launch_bounds__(kSumThreads) void gram_finalize_kernel(int K, const int64_t *__restrict__ cs,
                                                                     const double *__restrict__ partials,
                                                                     const uint32_t *__restrict__ err,
                                                                     double *__restrict__ gram) {
   __shared__ double red[kSumThreads];
   const int64_t b = blockIdx.x;
   const int P = K * (K + 1) / 2;
-  double s = sum_slots<kSumThreads>(partials, cs[b], (cs[b + 1] - cs[b] + step - 1) / step, step, P, red);
+  double s = sum_bucket<kSumThreads>(partials, cs, b, P, red);
   if ((int)threadIdx.x < P) {
     if (*err & kErrOffsets) s = __builtin_nan("");
     int i, j;
@@ -280,12 +279,12 @@ hipError_t dispatch_gram(const StreamArgs &a, double *partials, hipStream_t s) {
 
 }  // namespace
 
-int gram_sum_step(int K, int dt, int64_t N) { return N / gram_chunk_elems(K, dt) < kSumDirect ? 1 : kFinalizeGroup; }
-
 hipError_t launch_gram_partials(const StreamArgs &a, double *partials, hipStream_t s) {
   hipError_t e = a.dt == F32 ? dispatch_gram<F32>(a, partials, s) : dispatch_gram<BF16>(a, partials, s);
-  if (e != hipSuccess || gram_sum_step(a.K, a.dt, a.N) == 1) return e;
-  const int64_t groups = a.N / (gram_chunk_elems(a.K, a.dt) * kFinalizeGroup) + a.B;
+  // the chunks that one bucket can have, and the groups of all that have them
+  const int64_t chunks = (a.N + gram_chunk_elems(a.K, a.dt) - 1) / gram_chunk_elems(a.K, a.dt);
+  if (e != hipSuccess || chunks < kSumDirect) return e;
+  const int64_t groups = chunks / kFinalizeGroup + chunks / kSumDirect;
   const int64_t limit = (int64_t)device_cu_count() * 4;
   hipLaunchKernelGGL(gram_group_kernel, dim3((unsigned)(groups < limit ? groups : limit)), dim3(kSumThreads), 0, s,
                      pairs(a.K), a.B, a.chunk_start, a.group_start, partials);
@@ -294,7 +293,7 @@ hipError_t launch_gram_partials(const StreamArgs &a, double *partials, hipStream
 
 hipError_t launch_gram_finalize(const StreamArgs &a, const double *partials, double *gram, hipStream_t s) {
   hipLaunchKernelGGL(gram_finalize_kernel, dim3((unsigned)a.B), dim3(kSumThreads), 0, s, a.K, a.chunk_start,
-                     gram_sum_step(a.K, a.dt, a.N), partials, a.err, gram);
+                     partials, a.err, gram);
   return hipGetLastError();
 }
 

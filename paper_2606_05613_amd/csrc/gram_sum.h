@@ -51,6 +51,15 @@ __device__ __forceinline__ double sum_slots(const double *__restrict__ slots, in
   return s;
 }
 
+// Pair p's sum over bucket b, of its chunk slots or, in a bucket of kSumDirect
+// chunks and more, of its group sums.
+template <int T>
+__device__ __forceinline__ double sum_bucket(const double *__restrict__ partials, const int64_t *__restrict__ cs,
+                                             int64_t b, int P, double *red) {
+  const int64_t c0 = cs[b], n = cs[b + 1] - c0, step = n < kSumDirect ? 1 : kFinalizeGroup;
+  return sum_slots<T>(partials, c0, (n + step - 1) / step, step, P, red);
+}
+
 // Task pair (i <= j) of entry p of the row-major upper triangle.
 __device__ __forceinline__ void pair_of(int p, int K, int &i, int &j) {
   i = 0;

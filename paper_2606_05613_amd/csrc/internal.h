@@ -57,12 +57,15 @@ static_assert(combine_parts_fit(), "a Gram chunk is kCombineParts combine chunks
 
 constexpr int pairs(int K) { return K * (K + 1) / 2; }
 
-// The Gram finalize adds a bucket's chunk slots directly, one workgroup per
-// bucket, where no bucket can have kSumDirect chunks; beyond that groups of
-// this many consecutive chunks come first (one workgroup per group, so that a
+// The Gram finalize adds the chunk slots of a bucket of fewer than kSumDirect
+// chunks directly, one workgroup per bucket; in a longer bucket groups of this
+// many consecutive chunks come first (one workgroup per group, so that a
 // single large bucket is not added by one), then the group sums.  Groups of
 // 64 fill the chip sooner than the 1024 used before: K=8 bf16, one bucket of
 // 124M elements (3,798 chunks), 40 + 5 us for the two kernels with 1024.
+// Which of the two it is depends on the bucket alone, so its matrix is the same
+// bits whatever else the call holds; and short buckets have no groups (K=2 fp32,
+// 20,000 buckets of one chunk, a group each: 209 us for the group kernel).
 constexpr int kFinalizeGroup = 64;
 constexpr int64_t kSumDirect = 512;
 // Size of a finalize group in the workspace's layout (see Layout::reserve).
@@ -187,9 +190,7 @@ hipError_t launch_schedule(const int64_t *offsets, int B, int64_t N, int64_t C, 
                            int64_t *group_start, uint32_t *err, uint32_t *sync, int64_t nsync,
                            const PipePlan &plan, hipStream_t s);
 // Gram pass: per-chunk partials (and group sums, left in the slots of the
-// groups' first chunks), then the per-bucket matrices.  gram_sum_step is the
-// distance of the slots that the finalize adds up (1: the chunks).
-int gram_sum_step(int K, int dt, int64_t N);
+// groups' first chunks), then the per-bucket matrices.
 hipError_t launch_gram_partials(const StreamArgs &a, double *partials, hipStream_t s);
 hipError_t launch_gram_finalize(const StreamArgs &a, const double *partials, double *gram, hipStream_t s);
 // The finalize and the solve (not the exact methods) in one kernel.

@@ -35,11 +35,12 @@ __device__ __forceinline__ Sums block_scan(Sums s, Sums (&tot)[T / kWave]) {
 }
 
 // Checks the offsets and calls put(b, s) for b = 0 .. B with s.x = sum over b'
-// < b of ceil(n_b' / C) and s.y = sum over b' < b of ceil(chunks_b' / G); false
-// (and no call) if the offsets are not 0 = o_0 <= ... <= o_B = N.
+// < b of ceil(n_b' / C), the chunks, and s.y the finalize groups of those
+// buckets (kSumDirect); false (and no call) if the offsets are not 0 = o_0 <=
+// ... <= o_B = N.
 template <int T, typename Put>
 __device__ __forceinline__ bool block_schedule(const int64_t *__restrict__ offs, int B, int64_t N, int64_t C,
-                                               int64_t G, Put put) {
+                                               Put put) {
   __shared__ Sums tot[T / kWave];
   const int tid = threadIdx.x;
   int bad = offs[0] != 0 || offs[B] != N;
@@ -50,7 +51,7 @@ __device__ __forceinline__ bool block_schedule(const int64_t *__restrict__ offs,
     const int b = base + tid;
     const int64_t n = b < B ? offs[b + 1] - offs[b] : 0;
     const int64_t cnt = (n + C - 1) / C;
-    const Sums own{cnt, (cnt + G - 1) / G};
+    const Sums own{cnt, cnt < kSumDirect ? 0 : (cnt + kFinalizeGroup - 1) / kFinalizeGroup};
     const Sums s = block_scan<T>(own, tot);
     if (b < B) put(b, Sums{carry.x + s.x - own.x, carry.y + s.y - own.y});
     for (int w = 0; w < T / kWave; ++w) {
@@ -89,7 +90,7 @@ struct ScheduleOut {
 __device__ __forceinline__ bool own_schedule(const int64_t *__restrict__ offs, int B, int64_t C, const ScheduleOut &o,
                                              int64_t (&lcs)[kSelfBuckets + 1]) {
   const bool writes = blockIdx.x == 0;
-  const bool ok = block_schedule<kThreads>(offs, B, o.N, C, kFinalizeGroup, [&](int b, Sums before) {
+  const bool ok = block_schedule<kThreads>(offs, B, o.N, C, [&](int b, Sums before) {
     lcs[b] = before.x;
     if (writes) {
       o.cs[b] = before.x;

@@ -10,8 +10,8 @@ namespace {
 constexpr int kSchedThreads = 1024;
 
 // Workgroup 0.  chunk_start[b] = sum_{b' < b} ceil(n_b' / C) and, when
-// group_start is given, group_start[b] = sum_{b' < b} ceil(chunks_b' / G)
-// (groups of G consecutive chunks of one bucket, the Gram finalize's unit).
+// group_start is given, group_start[b] = the finalize groups of the buckets
+// before b (none in a bucket of fewer than kSumDirect chunks).
 // On invalid offsets every entry is 0 (so no chunk is processed) and the
 // error word gets kErrOffsets.  Otherwise the error word is cleared.  With a
 // plan (plan.groups > 0) the word after it says whether the cooperative
@@ -19,7 +19,7 @@ constexpr int kSchedThreads = 1024;
 // `nsync` words at `sync`.
 __global__ __launch_bounds__(kSchedThreads) void schedule_kernel(
     const int64_t *__restrict__ offs, int B, int64_t N, int64_t C, int64_t *__restrict__ cs,
-    int64_t G, int64_t *__restrict__ gs, uint32_t *__restrict__ err, uint32_t *__restrict__ sync,
+    int64_t *__restrict__ gs, uint32_t *__restrict__ err, uint32_t *__restrict__ sync,
     int64_t nsync, PipePlan plan) {
   const int tid = threadIdx.x;
   if (blockIdx.x > 0) {
@@ -29,7 +29,7 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_kernel(
   }
   __shared__ unsigned long long load[kMaxPlanGroups];  // estimated ns of each group's buckets
   if (tid < kMaxPlanGroups) load[tid] = 0;
-  const bool ok = block_schedule<kSchedThreads>(offs, B, N, C, G, [&](int b, Sums before) {
+  const bool ok = block_schedule<kSchedThreads>(offs, B, N, C, [&](int b, Sums before) {
     cs[b] = before.x;
     if (gs) gs[b] = before.y;
     if (plan.groups > 0 && b < B)
@@ -56,7 +56,7 @@ hipError_t launch_schedule(const int64_t *offsets, int B, int64_t N, int64_t C, 
   // workgroup 0 schedules, up to 64 others clear
   const int64_t clear = (nsync + kSchedThreads - 1) / kSchedThreads;
   hipLaunchKernelGGL(schedule_kernel, dim3((unsigned)(1 + (clear < 64 ? clear : 64))), dim3(kSchedThreads), 0, s,
-                     offsets, B, N, C, chunk_start, (int64_t)kFinalizeGroup, group_start, err, sync, nsync, plan);
+                     offsets, B, N, C, chunk_start, group_start, err, sync, nsync, plan);
   return hipGetLastError();
 }
 

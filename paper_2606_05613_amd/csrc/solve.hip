@@ -63,7 +63,7 @@ __global__ __launch_bounds__(kWave) void lane_solve_kernel(const double *__restr
 // the smallest step spent 13 of its 41 us here.  KT = 0: K at run time, the
 // sequential solvers (K > 10).
 template <int KT>
-__global__ __launch_bounds__(kSumThreads) void gram_solve_kernel(int Krt, const int64_t *__restrict__ cs, int step,
+__global__ __launch_bounds__(kSumThreads) void gram_solve_kernel(int Krt, const int64_t *__restrict__ cs,
                                                                  const double *__restrict__ partials,
                                                                  const uint32_t *__restrict__ err, int method,
                                                                  int iters, double c,
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(kSumThreads) void gram_solve_kernel(int Krt, const 
   const int64_t b = blockIdx.x;
   const int t = threadIdx.x;
   if (t == 0) S.bad = 0;
-  double s = sum_slots<kSumThreads>(partials, cs[b], (cs[b + 1] - cs[b] + step - 1) / step, step, P, red);
+  double s = sum_bucket<kSumThreads>(partials, cs, b, P, red);
   if (t < P) {
     if (*err & kErrOffsets) s = __builtin_nan("");
     int i, j;
@@ -111,8 +111,7 @@ __global__ __launch_bounds__(kSumThreads) void gram_solve_kernel(int Krt, const 
 template <int K>
 void launch_gram_solve_t(const StreamArgs &a, const double *partials, double *gram, int method, int max_iter, double c,
                          const int8_t *order, float *weights, double *aux, hipStream_t s) {
-  hipLaunchKernelGGL(gram_solve_kernel<K>, dim3((unsigned)a.B), dim3(kSumThreads), 0, s, a.K, a.chunk_start,
-                     gram_sum_step(a.K, a.dt, a.N), partials, a.err, method, max_iter, c, order, gram, weights, aux);
+  hipLaunchKernelGGL(gram_solve_kernel<K>, dim3((unsigned)a.B), dim3(kSumThreads), 0, s, a.K, a.chunk_start, partials, a.err, method, max_iter, c, order, gram, weights, aux);
 }
 
 template <int K>

@@ -1,5 +1,5 @@
 """The Gram finalize at the line where chunk slots are first added in groups
-(512 chunks in a call), the resolve call's finalize that also solves, and the
+(512 chunks in a bucket), the resolve call's finalize that also solves, and the
 schedule that a streaming pass makes for itself, against float64 sums of the
 same bytes."""
 
@@ -26,11 +26,11 @@ def _gram64(x, offs):
 @pytest.mark.parametrize("past", [-1, 0, 1])
 @pytest.mark.parametrize("K,dtype", [(2, "f32"), (16, "bf16")])
 def test_grouped_and_direct_sums(gpu_lib, K, dtype, past):
-    """Buckets of no, one, 63 to 65 and about 300 chunks, one a chunk and an
-    element long, at N just below, at and just above 512 chunks."""
+    """Buckets of no, one, 63 to 65 chunks, one a chunk and an element long, and
+    one of just below, at and just above 512 chunks, whose slots are first added
+    in groups from there on."""
     C = CHUNK[K, dtype]
-    lens = [1, 0, 63 * C, 64 * C, 64 * C + 1, C + 1, 0, 20 * C - 2]
-    lens.append(512 * C + past - sum(lens))
+    lens = [1, 0, 63 * C, 64 * C, 64 * C + 1, C + 1, 0, 20 * C - 2, (512 + past) * C - 2]
     offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
     print(f"case finalize K={K} {dtype} N={offs[-1]}", flush=True)
     gen = torch.Generator(device="cuda")
@@ -53,6 +53,22 @@ def test_grouped_and_direct_sums(gpu_lib, K, dtype, past):
     assert torch.equal(G, G2)
     w, _ = oracle.solve(G.cpu().numpy(), method, 20)
     assert_weights(W.cpu().numpy().astype(np.float64), w, "weights(iso)", f"K={K} past={past}")
+
+
+@pytest.mark.parametrize("K,dtype", [(2, "f32"), (16, "bf16")])
+def test_a_buckets_matrix_does_not_depend_on_the_others(gpu_lib, K, dtype):
+    """The order of a bucket's sum is its own: bit for bit the same matrix in a
+    call of that bucket and in one that has a bucket of 600 chunks as well."""
+    C = CHUNK[K, dtype]
+    n = 100 * C + 777
+    print(f"case finalize alone and in a long call K={K} {dtype}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(70 + K)
+    x = torch.randn((K, n + 600 * C), generator=gen, device="cuda")
+    x = x.to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    both = gpu_lib.gram(x, torch.tensor([0, n, n + 600 * C], device="cuda"))
+    alone = gpu_lib.gram([r[:n] for r in x], torch.tensor([0, n], device="cuda"))
+    assert torch.equal(both[0], alone[0])
 
 
 @pytest.mark.parametrize("B", [1, 256, 257, 511, 512, 1025])
