@@ -210,14 +210,15 @@ __global__ __launch_bounds__(kSumThreads) void gram_group_kernel(int P, int B, c
 // Finalize, level 2: one workgroup per bucket adds the bucket's chunk slots or
 // group sums and writes the symmetric K x K matrix (NaN everywhere when the
 // offsets were rejected by the schedule).
-__global__ __launch_bounds__(kSumThreads) void gram_finalize_kernel(int K, const int64_t *__restrict__ cs,
+template <int T>
+__global__ __launch_bounds__(T) void gram_finalize_kernel(int K, const int64_t *__restrict__ cs,
                                                                     const double *__restrict__ partials,
                                                                     const uint32_t *__restrict__ err,
                                                                     double *__restrict__ gram) {
   __shared__ double red[kSumThreads];
   const int64_t b = blockIdx.x;
   const int P = K * (K + 1) / 2;
-  double s = sum_bucket<kSumThreads>(partials, cs, b, P, red);
+  double s = sum_bucket<T>(partials, cs, b, P, red);
   if ((int)threadIdx.x < P) {
     if (*err & kErrOffsets) s = __builtin_nan("");
     int i, j;
@@ -292,8 +293,9 @@ hipError_t launch_gram_partials(const StreamArgs &a, double *partials, hipStream
 }
 
 hipError_t launch_gram_finalize(const StreamArgs &a, const double *partials, double *gram, hipStream_t s) {
-  hipLaunchKernelGGL(gram_finalize_kernel, dim3((unsigned)a.B), dim3(kSumThreads), 0, s, a.K, a.chunk_start,
-                     partials, a.err, gram);
+  const int T = sum_workgroup(a);
+  hipLaunchKernelGGL(T == kWave ? gram_finalize_kernel<kWave> : gram_finalize_kernel<kSumThreads>, dim3((unsigned)a.B),
+                     dim3((unsigned)T), 0, s, a.K, a.chunk_start, partials, a.err, gram);
   return hipGetLastError();
 }
 

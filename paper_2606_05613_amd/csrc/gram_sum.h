@@ -8,10 +8,22 @@ namespace bkmoo {
 
 namespace {
 
-// Workgroup of the kernels that add up a bucket's slots: at K = 16 (136
-// pairs) three rows of threads still read slots side by side.
+// Threads that add up a bucket's slots side by side: at K = 16 (136 pairs)
+// three rows of them.
 constexpr int kSumThreads = 512;
 static_assert(kSumThreads >= pairs(kMaxK), "a thread per pair");
+
+// The workgroup that does: a thread each, or one wavefront for all of them (the
+// same sums in the same order) where a call has many buckets of few slots, of
+// which most threads would only start and end: from four buckets a CU on and up
+// to four chunks a bucket on average.  The Gram call, us, threads / wavefront:
+// K=2 fp32, 20,000 buckets of 0.02 chunks 170 / 133, 2,048 of 0.9 60 / 59, 1,024
+// of 3.9 95 / 95; K=10 fp32 8,192 of 0.02 197 / 182; but 256 buckets of 3.9
+// 118 / 120, 16 of 7.9 32 / 36.
+inline int sum_workgroup(const StreamArgs &a) {
+  const bool small = a.B >= 4 * device_cu_count() && a.N / gram_chunk_elems(a.K, a.dt) <= 4 * (int64_t)a.B;
+  return small && pairs(a.K) <= kWave ? kWave : kSumThreads;
+}
 
 // Partial loads a thread keeps in flight.  The sums wait for memory, not for
 // bandwidth: with the loads one behind the other a group of 1024 slots of
@@ -20,17 +32,20 @@ static_assert(kSumThreads >= pairs(kMaxK), "a thread per pair");
 constexpr int kSumBatch = 16;
 
 // Sum over i = 0..n-1 of the P entries of slot c0 + i * step, for a whole
-// workgroup of T threads: thread t adds pair t % P of the slots t / P,
-// t / P + T / P, ... ascending, then the T / P rows are added ascending.  The
-// order depends on n, P and T alone.  Thread p < P returns pair p's sum;
-// `red` holds T doubles of LDS (it may be reused after the next barrier).
+// workgroup of T threads, a thread per pair at least: entry q < rows * P (rows
+// = kSumThreads / P) is pair q % P of the slots q / P, q / P + rows, ...
+// ascending, then the rows are added ascending.  The order depends on n and P
+// alone.  Thread p < P returns pair p's sum; `red` holds kSumThreads doubles of
+// LDS (it may be reused after the next barrier).
 template <int T>
 __device__ __forceinline__ double sum_slots(const double *__restrict__ slots, int64_t c0, int64_t n, int64_t step,
                                             int P, double *red) {
-  const int t = threadIdx.x, rows = T / P, r = t / P, p = t - r * P;
+  const int t = threadIdx.x, rows = kSumThreads / P;
   double s = 0.0;
-  if (r < rows) {
-    const double *base = slots + c0 * P + p;
+  for (int q = t; q < rows * P; q += T) {
+    const int r = q / P;
+    const double *base = slots + c0 * P + (q - r * P);
+    s = 0.0;
     for (int64_t i = r; i < n; i += (int64_t)rows * kSumBatch) {
       double x[kSumBatch];
 #pragma unroll
@@ -41,7 +56,7 @@ __device__ __forceinline__ double sum_slots(const double *__restrict__ slots, in
 #pragma unroll
       for (int u = 0; u < kSumBatch; ++u) s += x[u];
     }
-    red[t] = s;
+    red[q] = s;
   }
   __syncthreads();
   if (t < P) {

@@ -62,8 +62,8 @@ __global__ __launch_bounds__(kWave) void lane_solve_kernel(const double *__restr
 // its first wavefront solves from there.  As two kernels with a launch each
 // the smallest step spent 13 of its 41 us here.  KT = 0: K at run time, the
 // sequential solvers (K > 10).
-template <int KT>
-__global__ __launch_bounds__(kSumThreads) void gram_solve_kernel(int Krt, const int64_t *__restrict__ cs,
+template <int KT, int T>
+__global__ __launch_bounds__(T) void gram_solve_kernel(int Krt, const int64_t *__restrict__ cs,
                                                                  const double *__restrict__ partials,
                                                                  const uint32_t *__restrict__ err, int method,
                                                                  int iters, double c,
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(kSumThreads) void gram_solve_kernel(int Krt, const 
   const int64_t b = blockIdx.x;
   const int t = threadIdx.x;
   if (t == 0) S.bad = 0;
-  double s = sum_bucket<kSumThreads>(partials, cs, b, P, red);
+  double s = sum_bucket<T>(partials, cs, b, P, red);
   if (t < P) {
     if (*err & kErrOffsets) s = __builtin_nan("");
     int i, j;
@@ -87,8 +87,10 @@ __global__ __launch_bounds__(kSumThreads) void gram_solve_kernel(int Krt, const 
     if (!__builtin_isfinite(s)) S.bad = 1;
   }
   __syncthreads();
-  if (t >= kWave) {  // the other wavefronts write the matrix
-    for (int e = t - kWave; e < K * K; e += kSumThreads - kWave) gram[b * K * K + e] = S.G[e];
+  if constexpr (T == kWave) {
+    for (int e = t; e < K * K; e += T) gram[b * K * K + e] = S.G[e];
+  } else if (t >= kWave) {  // the other wavefronts write the matrix
+    for (int e = t - kWave; e < K * K; e += T - kWave) gram[b * K * K + e] = S.G[e];
     return;
   }
   double wt = 0.0, ax = 0.0;
@@ -111,7 +113,9 @@ __global__ __launch_bounds__(kSumThreads) void gram_solve_kernel(int Krt, const 
 template <int K>
 void launch_gram_solve_t(const StreamArgs &a, const double *partials, double *gram, int method, int max_iter, double c,
                          const int8_t *order, float *weights, double *aux, hipStream_t s) {
-  hipLaunchKernelGGL(gram_solve_kernel<K>, dim3((unsigned)a.B), dim3(kSumThreads), 0, s, a.K, a.chunk_start, partials, a.err, method, max_iter, c, order, gram, weights, aux);
+  const int T = sum_workgroup(a);
+  hipLaunchKernelGGL((T == kWave ? gram_solve_kernel<K, kWave> : gram_solve_kernel<K, kSumThreads>),
+                     dim3((unsigned)a.B), dim3((unsigned)T), 0, s, a.K, a.chunk_start, partials, a.err, method, max_iter, c, order, gram, weights, aux);
 }
 
 template <int K>

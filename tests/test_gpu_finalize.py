@@ -71,6 +71,43 @@ def test_a_buckets_matrix_does_not_depend_on_the_others(gpu_lib, K, dtype):
     assert torch.equal(both[0], alone[0])
 
 
+@pytest.mark.parametrize("K,dtype", [(2, "f32"), (10, "bf16"), (16, "f32")])
+def test_sums_by_one_wavefront(gpu_lib, K, dtype):
+    """Thousands of short buckets (and no, one and 100 chunks in some), whose
+    slots one wavefront a bucket adds: bit for bit the matrices, and weights,
+    that the buckets get in calls of few, by the whole workgroup."""
+    C = 32768 if dtype == "bf16" else 16384
+    rng = np.random.default_rng(K)
+    lens = rng.integers(0, 300, size=4096)
+    lens[[7, 8, 4095]] = 0, 100 * C + 5, 3 * C
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    print(f"case finalize by a wavefront K={K} {dtype} N={offs[-1]}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(75 + K)
+    x = torch.randn((K, int(offs[-1])), generator=gen, device="cuda")
+    x = x.to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    method = "mgda" if K < 16 else "pcgrad"
+    o = torch.from_numpy(offs).cuda()
+
+    def call(o):
+        G = torch.empty((len(o) - 1, K, K), dtype=torch.float64, device="cuda")
+        W = torch.empty((len(o) - 1, K), device="cuda")
+        gpu_lib.set_resolve_path(gpu_lib.PATH_TWO_PASS)
+        try:
+            gpu_lib.resolve(x, o, method, gram_out=G, weights=W)
+        finally:
+            gpu_lib.set_resolve_path(0)
+        assert torch.equal(G, gpu_lib.gram(x, o))
+        return G, W
+
+    G, W = call(o)
+    assert_gram(G.cpu().numpy(), _gram64(x, offs), dtype, f"K={K}")
+    for b in (0, 7, 8, 4000, 4095):  # the bucket, and all before and all after it as one
+        cut = torch.tensor([0, offs[b], offs[b + 1], offs[-1]], device="cuda")
+        G3, W3 = call(cut)
+        assert torch.equal(G3[1], G[b]) and torch.equal(W3[1], W[b]), f"bucket {b}"
+
+
 @pytest.mark.parametrize("B", [1, 256, 257, 511, 512, 1025])
 @pytest.mark.parametrize("K,dtype", [(2, "f32"), (8, "bf16")])
 def test_schedule_by_the_pass_or_its_own_kernel(gpu_lib, K, dtype, B):
