@@ -116,10 +116,10 @@ bool k_unsupported(int K, int method) { return K > kMaxK || (is_exact(method) &&
 // The schedule kernel before a streaming pass of many buckets; with few the
 // pass makes its schedule itself (own_schedule).
 hipError_t schedule_pass(const int64_t *offsets, int B, int64_t N, int K, int dt, int64_t *chunk_start,
-                         int64_t *group_start, uint32_t *err, hipStream_t s) {
+                         int64_t *group_start, int64_t *part_start, uint32_t *err, hipStream_t s) {
   if (B <= kSelfBuckets) return hipSuccess;
-  return launch_schedule(offsets, B, N, gram_chunk_elems(K, dt), chunk_start, group_start, err, nullptr, 0,
-                         PipePlan{}, s);
+  return launch_schedule(offsets, B, N, gram_chunk_elems(K, dt), chunk_start, group_start, part_start, err, nullptr,
+                         0, PipePlan{}, s);
 }
 
 bkmoo_status hip_status(hipError_t e) { return e == hipSuccess ? BKMOO_OK : BKMOO_EHIP; }
@@ -131,6 +131,7 @@ struct Carved {
   float *weights;
   double *partials;
   int64_t *group_start;
+  int64_t *part_start;
   uint32_t *sync;
 };
 
@@ -141,6 +142,7 @@ Carved carve(void *ws, const Layout &L) {
                 reinterpret_cast<double *>(base + L.gram), reinterpret_cast<float *>(base + L.weights),
                 reinterpret_cast<double *>(base + L.partials),
                 reinterpret_cast<int64_t *>(base + L.group_start),
+                reinterpret_cast<int64_t *>(base + L.part_start),
                 reinterpret_cast<uint32_t *>(base + L.sync)};
 }
 
@@ -463,10 +465,11 @@ bkmoo_status bkmoo_gram(int32_t K, const void *const *grads, bkmoo_dtype dt, int
   const Layout L = layout(K, N, B, dt);
   if (ws_bytes < L.total) return BKMOO_EWORKSPACE;
   const Carved w = carve(workspace, L);
-  if (schedule_pass(bucket_offsets, B, N, K, (int)dt, w.chunk_start, w.group_start, w.err, stream) != hipSuccess)
+  if (schedule_pass(bucket_offsets, B, N, K, (int)dt, w.chunk_start, w.group_start, w.part_start, w.err, stream) !=
+      hipSuccess)
     return BKMOO_EHIP;
-  const StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, w.group_start, w.err, B > kSelfBuckets,
-                     shift, g_grid_override.load()};
+  const StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, w.group_start, w.part_start, w.err,
+                     B > kSelfBuckets, shift, g_grid_override.load()};
   if (launch_gram_partials(a, w.partials, stream) != hipSuccess) return BKMOO_EHIP;
   return hip_status(launch_gram_finalize(a, w.partials, gram, stream));
 }
@@ -499,10 +502,11 @@ bkmoo_status bkmoo_combine(int32_t K, const void *const *grads, bkmoo_dtype dt, 
   const Layout L = layout(K, N, B, dt);
   if (ws_bytes < L.total) return BKMOO_EWORKSPACE;
   const Carved w = carve(workspace, L);
-  if (schedule_pass(bucket_offsets, B, N, K, (int)dt, w.chunk_start, nullptr, w.err, stream) != hipSuccess)
+  if (schedule_pass(bucket_offsets, B, N, K, (int)dt, w.chunk_start, w.group_start, w.part_start, w.err, stream) !=
+      hipSuccess)
     return BKMOO_EHIP;
-  const StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, nullptr, w.err, B > kSelfBuckets,
-                     out_shift, g_grid_override.load()};
+  const StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, w.group_start, w.part_start, w.err,
+                     B > kSelfBuckets, out_shift, g_grid_override.load()};
   return hip_status(launch_combine(a, weights, out, (int)out_dt, stream));
 }
 
@@ -563,8 +567,8 @@ bkmoo_status resolve_impl(int32_t K, const void *const *grads, bkmoo_dtype dt, i
     const PipePlan plan = path == BKMOO_PATH_REFILL && g_resolve_path.load() == 0
                               ? pipe_plan(K, (int)dt, (int)out_dt, (int)method, iters, groups)
                               : PipePlan{};
-    hipError_t e = launch_schedule(bucket_offsets, B, N, gram_chunk_elems(K, dt), w.chunk_start, nullptr, w.err,
-                                   w.sync, (1 + kFlagCopies) * (int64_t)B * kSyncStride, plan, stream);
+    hipError_t e = launch_schedule(bucket_offsets, B, N, gram_chunk_elems(K, dt), w.chunk_start, nullptr, nullptr,
+                                   w.err, w.sync, (1 + kFlagCopies) * (int64_t)B * kSyncStride, plan, stream);
     if (e != hipSuccess) return BKMOO_EHIP;
     uint32_t *flags = w.sync + (int64_t)B * kSyncStride;
     if (path == BKMOO_PATH_REFILL)
@@ -578,10 +582,11 @@ bkmoo_status resolve_impl(int32_t K, const void *const *grads, bkmoo_dtype dt, i
     return hip_status(e);
   }
 
-  hipError_t e = schedule_pass(bucket_offsets, B, N, K, (int)dt, w.chunk_start, w.group_start, w.err, stream);
+  hipError_t e = schedule_pass(bucket_offsets, B, N, K, (int)dt, w.chunk_start, w.group_start, w.part_start, w.err,
+                               stream);
   if (e != hipSuccess) return BKMOO_EHIP;
-  StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, w.group_start, w.err, B > kSelfBuckets, shift,
-               g_grid_override.load()};
+  StreamArgs a{K, (int)dt, grads, N, B, bucket_offsets, w.chunk_start, w.group_start, w.part_start, w.err,
+               B > kSelfBuckets, shift, g_grid_override.load()};
   if (launch_gram_partials(a, w.partials, stream) != hipSuccess) return BKMOO_EHIP;
   if (is_exact(method)) {
     if (launch_gram_finalize(a, w.partials, G, stream) != hipSuccess) return BKMOO_EHIP;

@@ -4,8 +4,10 @@
 //
 // Bandwidth-bound: K*N*s bytes read, N*s_out written, 2K flops per
 // element.  128-bit non-temporal loads as in the Gram pass, whose chunks are
-// cut in kCombineParts (the schedule is the Gram pass's: a schedule kernel of
-// its own cost every two-pass call 5-6 us); the K weights of a chunk's bucket are wave-uniform scalars.  Unlike the
+// cut in kCombineParts (one schedule serves both passes: a schedule kernel of
+// its own cost every two-pass call 5-6 us).  The schedule counts the parts: with
+// two for every chunk, half of them empty where buckets are short, K=4 bf16,
+// 20,000 buckets of 64 elements took 231 us instead of 136.  The K weights of a chunk's bucket are wave-uniform scalars.  Unlike the
 // Gram pass, chunks are dealt round-robin (chunk c to workgroup c mod grid),
 // so the whole grid sweeps the vector together: measured 1-2.5% faster
 // than one contiguous run per workgroup on every workload shape here, in
@@ -29,22 +31,21 @@ namespace {
 
 template <int K, int DT, int ODT, bool SELF>
 __global__ __launch_bounds__(kThreads) void combine_kernel(
-    Rows<K> rows, const int64_t *__restrict__ offs, const int64_t *__restrict__ gcs, int B,
+    Rows<K> rows, const int64_t *__restrict__ offs, const int64_t *__restrict__ gps, int B,
     int shift, ScheduleOut sched, const float *__restrict__ weights, void *out) {
   constexpr int64_t C = combine_chunk_elems(K, DT);
 
-  __shared__ int64_t lcs[SELF ? kSelfBuckets + 1 : 1];
+  __shared__ int64_t lps[SELF ? kSelfBuckets + 1 : 1];
   if constexpr (SELF) {
-    if (!own_schedule(offs, B, C * kCombineParts, sched, lcs)) return;
+    if (!own_schedule<true>(offs, B, C * kCombineParts, sched, lps)) return;
   }
-  const int64_t *cs = SELF ? lcs : gcs;
-  const int64_t total = cs[B] * kCombineParts;
+  const int64_t *ps = SELF ? lps : gps;
+  const int64_t total = ps[B];
 
   for (int64_t c = blockIdx.x; c < total; c += gridDim.x) {
-    const int b = find_bucket(cs, B, c / kCombineParts);
-    const int64_t lo = offs[b] + (c - cs[b] * kCombineParts) * C;
+    const int b = find_bucket(ps, B, c);
+    const int64_t lo = offs[b] + (c - ps[b]) * C;
     const int64_t hi = lo + C < offs[b + 1] ? lo + C : offs[b + 1];
-    if (lo >= hi) continue;  // the bucket ends in an earlier part of its last Gram chunk
     float w[K];
 #pragma unroll
     for (int i = 0; i < K; ++i) w[i] = weights[(int64_t)b * K + i];
@@ -65,7 +66,8 @@ hipError_t launch_combine_s(const StreamArgs &a, const float *weights, void *out
   if (grid > cap) grid = cap;
   if (grid < 1) grid = 1;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), 0, s, rows, a.offsets,
-                     a.chunk_start, a.B, a.shift, ScheduleOut{a.N, a.chunk_start, nullptr, a.err}, weights, out);
+                     a.part_start, a.B, a.shift, ScheduleOut{a.N, a.chunk_start, a.group_start, a.part_start, a.err},
+                     weights, out);
   return hipGetLastError();
 }
 

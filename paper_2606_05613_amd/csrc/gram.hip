@@ -37,7 +37,7 @@ __global__ __launch_bounds__(kThreads) void gram_partial_kernel(
 
   __shared__ int64_t lcs[SELF ? kSelfBuckets + 1 : 1];
   if constexpr (SELF) {
-    if (!own_schedule(offs, B, C, sched, lcs)) return;
+    if (!own_schedule<false>(offs, B, C, sched, lcs)) return;
   }
   const int64_t *cs = SELF ? lcs : gcs;
   int64_t c, cend;
@@ -108,7 +108,7 @@ __global__ __launch_bounds__(kThreads) void gram_mfma_kernel(Rows<K> rows, const
 
   __shared__ int64_t lcs[SELF ? kSelfBuckets + 1 : 1];
   if constexpr (SELF) {
-    if (!own_schedule(offs, B, C, sched, lcs)) return;
+    if (!own_schedule<false>(offs, B, C, sched, lcs)) return;
   }
   const int64_t *cs = SELF ? lcs : gcs;
   int64_t c, cend;
@@ -247,7 +247,8 @@ hipError_t launch_gram_s(const StreamArgs &a, double *partials, hipStream_t s) {
   if (grid > cap) grid = cap;
   if (grid < 1) grid = 1;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), 0, s, rows, a.offsets,
-                     a.chunk_start, a.B, a.shift, ScheduleOut{a.N, a.chunk_start, a.group_start, a.err}, partials);
+                     a.chunk_start, a.B, a.shift, ScheduleOut{a.N, a.chunk_start, a.group_start, a.part_start, a.err},
+                     partials);
   return hipGetLastError();
 }
 

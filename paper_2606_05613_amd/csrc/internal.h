@@ -44,8 +44,9 @@ constexpr int64_t shape_elems(PassShape p, int dt) {
 }
 constexpr int64_t gram_chunk_elems(int K, int dt) { return shape_elems(gram_shape(K), dt); }
 constexpr int64_t combine_chunk_elems(int K, int dt) { return shape_elems(combine_shape(K), dt); }
-// The combine pass cuts every Gram chunk into this many of its own, so that
-// one schedule serves both passes.
+// The combine pass cuts every Gram chunk into this many of its own (parts), so
+// that one schedule serves both passes; a bucket's last chunk has one part if
+// that holds its rest.
 constexpr int kCombineParts = 2;
 constexpr bool combine_parts_fit() {
   for (int K = kMinK; K <= kMaxK; ++K)
@@ -68,7 +69,7 @@ constexpr int pairs(int K) { return K * (K + 1) / 2; }
 // 20,000 buckets of one chunk, a group each: 209 us for the group kernel).
 constexpr int kFinalizeGroup = 64;
 constexpr int64_t kSumDirect = 512;
-// Size of a finalize group in the workspace's layout (see Layout::reserve).
+// Size of a finalize group in the workspace's layout (see Layout::part_start).
 constexpr int kLayoutGroup = 1024;
 
 // Partial-Gram slots the workspace always has room for (the pipelined
@@ -93,13 +94,14 @@ constexpr int kFlagCopies = 8;
 //   partials            fp64  [cap][P]    cap = ceil(N / C) + B (at least kCoopSlots slots of P
 //                                         rounded up to even)
 //   group_start         int64 [B + 1]     (prefix sum of finalize groups per bucket)
-//   reserve             fp64  [cap / kLayoutGroup + B + 1][P]  unused (the group sums lie in
-//                       the partial slots); it keeps a workspace's size, and with it which calls
-//                       the library's fixed scratch can hold, as callers know them
+//   part_start          int64 [B + 1]     (prefix sum of combine parts), in a region of fp64
+//                       [cap / kLayoutGroup + B + 1][P]; the rest of it is unused, which keeps a
+//                       workspace's size, and with it which calls the library's fixed scratch
+//                       can hold, as callers know them
 //   sync                uint32 [1 + kFlagCopies][B][kSyncStride]  cooperative path: arrival
 //                       counters, then kFlagCopies copies of the flags
 struct Layout {
-  size_t err, chunk_start, gram, weights, partials, group_start, reserve, sync, total;
+  size_t err, chunk_start, gram, weights, partials, group_start, part_start, sync, total;
   int64_t cap_chunks;
 };
 
@@ -121,7 +123,7 @@ inline Layout layout(int K, int64_t N, int B, int dt) {
                            ? L.cap_chunks * pairs(K) : kCoopSlots * (pairs(K) + (pairs(K) & 1));
   L.partials = o;       o = align256(o + sizeof(double) * (size_t)part);
   L.group_start = o;    o = align256(o + sizeof(int64_t) * (size_t)(B + 1));
-  L.reserve = o;        o = align256(o + sizeof(double) * (size_t)(L.cap_chunks / kLayoutGroup + B + 1) * pairs(K));
+  L.part_start = o;     o = align256(o + sizeof(double) * (size_t)(L.cap_chunks / kLayoutGroup + B + 1) * pairs(K));
   L.sync = o;           o = align256(o + sizeof(uint32_t) * (1 + kFlagCopies) * (size_t)B * kSyncStride);
   L.total = o;
   return L;
@@ -175,19 +177,21 @@ struct StreamArgs {
   int B;
   const int64_t *offsets;      // device [B+1]
   int64_t *chunk_start;        // device [B+1]
-  int64_t *group_start;        // device [B+1] finalize groups (Gram pass only)
+  int64_t *group_start;        // device [B+1] finalize groups
+  int64_t *part_start;         // device [B+1] combine parts
   uint32_t *err;               // device error word
-  bool scheduled;              // these three are there (else the pass makes them, B <= kSelfBuckets)
+  bool scheduled;              // these four are there (else the pass makes them, B <= kSelfBuckets)
   int shift;                   // vectors start at elements n = shift (mod V): where the rows are 16-byte
                                // aligned (Gram pass: row 0) and, in the combine, the output's stores
   int grid;                    // workgroups (0: automatic)
 };
 
-// Validates offsets, writes chunk_start for chunks of C elements (and, if
-// group_start is not null, the prefix of finalize groups), sets the error
-// word and, by `plan`, the word after it, and zeroes `nsync` words at `sync`.
+// Validates offsets, writes chunk_start for chunks of C elements (and, where
+// they are not null, the prefixes of finalize groups and of combine parts),
+// sets the error word and, by `plan`, the word after it, and zeroes `nsync`
+// words at `sync`.
 hipError_t launch_schedule(const int64_t *offsets, int B, int64_t N, int64_t C, int64_t *chunk_start,
-                           int64_t *group_start, uint32_t *err, uint32_t *sync, int64_t nsync,
+                           int64_t *group_start, int64_t *part_start, uint32_t *err, uint32_t *sync, int64_t nsync,
                            const PipePlan &plan, hipStream_t s);
 // Gram pass: per-chunk partials (and group sums, left in the slots of the
 // groups' first chunks), then the per-bucket matrices.

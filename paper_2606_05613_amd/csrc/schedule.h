@@ -8,11 +8,19 @@ namespace bkmoo {
 
 namespace {
 
-// Inclusive sums of x and y over the workgroup's threads: shuffles in the
-// wavefront, then the wavefronts' totals (tot, two barriers).
+// Running sums over buckets: x their chunks; y their finalize groups (from bit
+// 32 up) and how many of them end in the first half of a chunk, so that the last
+// chunk has one combine part (the bits below, at most B < 2^31 in all).
 struct Sums {
   int64_t x, y;
+  __device__ __forceinline__ int64_t chunks() const { return x; }
+  __device__ __forceinline__ int64_t groups() const { return y >> 32; }
+  __device__ __forceinline__ int64_t parts() const { return kCombineParts * x - (y & 0xffffffff); }
 };
+static_assert(kCombineParts == 2, "a chunk's parts are its halves");
+
+// Inclusive sums over the workgroup's threads: shuffles in the wavefront, then
+// the wavefronts' totals (tot, two barriers).
 template <int T>
 __device__ __forceinline__ Sums block_scan(Sums s, Sums (&tot)[T / kWave]) {
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -34,10 +42,9 @@ __device__ __forceinline__ Sums block_scan(Sums s, Sums (&tot)[T / kWave]) {
   return s;
 }
 
-// Checks the offsets and calls put(b, s) for b = 0 .. B with s.x = sum over b'
-// < b of ceil(n_b' / C), the chunks, and s.y the finalize groups of those
-// buckets (kSumDirect); false (and no call) if the offsets are not 0 = o_0 <=
-// ... <= o_B = N.
+// Checks the offsets and calls put(b, s) for b = 0 .. B with the sums over the
+// buckets before b (chunks of C elements, finalize groups by kSumDirect); false
+// (and no call) if the offsets are not 0 = o_0 <= ... <= o_B = N.
 template <int T, typename Put>
 __device__ __forceinline__ bool block_schedule(const int64_t *__restrict__ offs, int B, int64_t N, int64_t C,
                                                Put put) {
@@ -51,7 +58,9 @@ __device__ __forceinline__ bool block_schedule(const int64_t *__restrict__ offs,
     const int b = base + tid;
     const int64_t n = b < B ? offs[b + 1] - offs[b] : 0;
     const int64_t cnt = (n + C - 1) / C;
-    const Sums own{cnt, cnt < kSumDirect ? 0 : (cnt + kFinalizeGroup - 1) / kFinalizeGroup};
+    const int64_t groups = cnt < kSumDirect ? 0 : (cnt + kFinalizeGroup - 1) / kFinalizeGroup;
+    const bool half = n > 0 && n - (cnt - 1) * C <= C / kCombineParts;
+    const Sums own{cnt, (groups << 32) + (half ? 1 : 0)};
     const Sums s = block_scan<T>(own, tot);
     if (b < B) put(b, Sums{carry.x + s.x - own.x, carry.y + s.y - own.y});
     for (int w = 0; w < T / kWave; ++w) {
@@ -64,10 +73,11 @@ __device__ __forceinline__ bool block_schedule(const int64_t *__restrict__ offs,
 }
 
 // Invalid offsets: no chunk is processed, the error word says why.
-__device__ __forceinline__ void reject_offsets(int B, int64_t *cs, int64_t *gs, uint32_t *err) {
+__device__ __forceinline__ void reject_offsets(int B, int64_t *cs, int64_t *gs, int64_t *ps, uint32_t *err) {
   for (int b = threadIdx.x; b <= B; b += blockDim.x) {
     cs[b] = 0;
     if (gs) gs[b] = 0;
+    if (ps) ps[b] = 0;
   }
   if (threadIdx.x == 0) {
     err[0] = kErrOffsets;
@@ -76,29 +86,31 @@ __device__ __forceinline__ void reject_offsets(int B, int64_t *cs, int64_t *gs, 
 }
 
 // A streaming pass's own schedule (SELF: at most kSelfBuckets buckets): every
-// workgroup makes the chunk prefix for itself in LDS, workgroup 0 also leaves
-// it, the group prefix and the error word in the workspace for the kernels
-// that follow.  As a kernel of its own the schedule takes 4.5 us and a launch
+// workgroup makes the prefix it needs for itself in LDS, of chunks or (PARTS) of
+// combine parts; workgroup 0 also leaves these, the group prefix and the error
+// word in the workspace for the kernels that follow.  As a kernel of its own the schedule takes 4.5 us and a launch
 // of a step of 30 (K=2, 1M fp32); a workgroup that starts with it needs about
 // 1.5 us, and finds a chunk's bucket in LDS rather than in memory.
 constexpr int kSelfBuckets = 511;
 struct ScheduleOut {
   int64_t N;
-  int64_t *cs, *gs;  // gs may be null
+  int64_t *cs, *gs, *ps;
   uint32_t *err;
 };
+template <bool PARTS>
 __device__ __forceinline__ bool own_schedule(const int64_t *__restrict__ offs, int B, int64_t C, const ScheduleOut &o,
                                              int64_t (&lcs)[kSelfBuckets + 1]) {
   const bool writes = blockIdx.x == 0;
   const bool ok = block_schedule<kThreads>(offs, B, o.N, C, [&](int b, Sums before) {
-    lcs[b] = before.x;
+    lcs[b] = PARTS ? before.parts() : before.chunks();
     if (writes) {
-      o.cs[b] = before.x;
-      if (o.gs) o.gs[b] = before.y;
+      o.cs[b] = before.chunks();
+      o.gs[b] = before.groups();
+      o.ps[b] = before.parts();
     }
   });
   if (!ok) {
-    if (writes) reject_offsets(B, o.cs, o.gs, o.err);
+    if (writes) reject_offsets(B, o.cs, o.gs, o.ps, o.err);
     return false;
   }
   if (writes && threadIdx.x == 0) o.err[0] = o.err[1] = 0u;

@@ -108,6 +108,39 @@ def test_sums_by_one_wavefront(gpu_lib, K, dtype):
         assert torch.equal(G3[1], G[b]) and torch.equal(W3[1], W[b]), f"bucket {b}"
 
 
+@pytest.mark.parametrize("more", [0, 600])
+@pytest.mark.parametrize("K,dtype", [(3, "f32"), (10, "bf16")])
+def test_a_chunks_parts(gpu_lib, K, dtype, more):
+    """Buckets that end around the half of a chunk, where the combine's last
+    part of it begins, with `more` one-element buckets among them (so that the
+    pass finds its parts in LDS or in the workspace): every element once."""
+    C = 32768 if dtype == "bf16" else 16384
+    lens = [C // 2 - 1, C // 2, C // 2 + 1, C - 1, C, C + 1, 0, 1] + [1] * more
+    lens += [3 * C // 2 - 1, 3 * C // 2, 3 * C // 2 + 1, 2 * C, 0, 5 * C // 2, 7]
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    n, B = int(offs[-1]), len(lens)
+    print(f"case combine parts K={K} {dtype} B={B} N={n}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(80 + K)
+    x = torch.randn((K, n), generator=gen, device="cuda").to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    w = torch.randn((B, K), generator=gen, device="cuda")
+    o = torch.from_numpy(offs).cuda()
+    out = torch.full((n,), float("nan"), device="cuda")
+    gpu_lib.combine(x, o, w, out=out)
+    terms = w.double()[torch.repeat_interleave(torch.arange(B, device="cuda"), torch.tensor(lens, device="cuda"))].t()
+    terms = terms * x.double()
+    # an fp32 FMA chain of K terms
+    assert bool(((out.double() - terms.sum(0)).abs() <= K * 2.0 ** -24 * terms.abs().sum(0) + 1e-30).all())
+    two_pass = torch.full((n,), float("nan"), device="cuda")
+    W = torch.empty((B, K), device="cuda")
+    gpu_lib.set_resolve_path(gpu_lib.PATH_TWO_PASS)
+    try:
+        gpu_lib.resolve(x, o, "mgda", out=two_pass, weights=W)
+    finally:
+        gpu_lib.set_resolve_path(0)
+    assert torch.equal(two_pass, gpu_lib.combine(x, o, W, out_dtype=torch.float32))
+
+
 @pytest.mark.parametrize("B", [1, 256, 257, 511, 512, 1025])
 @pytest.mark.parametrize("K,dtype", [(2, "f32"), (8, "bf16")])
 def test_schedule_by_the_pass_or_its_own_kernel(gpu_lib, K, dtype, B):
