@@ -283,7 +283,8 @@ hipError_t launch_hybrid(int K, int dt, int out_dt, const void *const *rows, con
 
 int device_cu_count();
 
-// Workgroups of a streaming pass of `cap` chunks at most.  A long pass is
+// Workgroups of a streaming pass over B buckets that cuts a Gram chunk into
+// `parts` and has at most `cap` of these in all.  A long pass is
 // fastest with no more wavefronts than keep about 128 KiB of loads in flight
 // on a CU (a workgroup has 8 KiB per task and vector of a step, two steps at a
 // time): further ones only spread the accesses over more of memory.  2 GiB
@@ -291,16 +292,23 @@ int device_cu_count();
 // fp32 371 / 569 -> 350 / 529, K=8 fp32 403 / 516 -> 365 / 496, K=10 fp32 377 /
 // 491 -> 357 / 460, K=4 bf16 374 / 558 -> 357 / 552; K=2 bf16 374 / 705 -> 340
 // / 675 with four, 432 / 782 with two.  A short pass (fewer than kLongPass
-// chunks for each of them) takes all that fit.
+// whole parts for each of them) takes all that fit, and so does one of short
+// buckets: it waits for latency at each, and where full and nearly empty chunks
+// take turns a workgroup may be dealt only full ones, which further ones on its
+// CU make up for.  Combine, all / two a CU, us: K=4 bf16, 0.7 GiB, buckets of
+// 0.05 chunks 384 / 512, of 1.5 190 / 216, of 3 201 / 197; with one vector per
+// row and step K=8 fp32, 2 GiB, buckets of 0.25 485 / 465, of 1.5 544 / 530, but
+// 20,000 of 64 elements 125 / 143.
 constexpr int kLongPass = 4;
 constexpr int stream_wgs(int K, int R) {
   const int n = (16 + K * R / 2) / (K * R);
   return n < 2 ? 2 : n;
 }
-inline int64_t stream_grid(int K, int R, int occ, int64_t cap) {
-  const int64_t cus = device_cu_count(), few = cus * stream_wgs(K, R);
+inline int64_t stream_grid(const StreamArgs &a, int R, int parts, int occ, int64_t cap) {
+  const int64_t cus = device_cu_count(), few = cus * stream_wgs(a.K, R);
+  const int64_t chunks = a.N / gram_chunk_elems(a.K, a.dt), B = a.B;
   int64_t grid = cus * occ;
-  if (grid > few && cap >= kLongPass * few) grid = few;
+  if (grid > few && chunks * parts >= kLongPass * few && chunks >= (R > 1 ? 3 * B : B / 4)) grid = few;
   if (grid > cap) grid = cap;
   return grid < 1 ? 1 : grid;
 }
