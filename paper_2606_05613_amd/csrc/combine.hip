@@ -62,7 +62,10 @@ hipError_t launch_combine_s(const StreamArgs &a, const float *weights, void *out
   const int64_t C = combine_chunk_elems(K, DT);
   const int64_t cap = (a.N + C - 1) / C + a.B;
   static const int occ = occupancy(kern);
-  int64_t grid = a.grid > 0 ? a.grid : stream_grid(a, combine_shape(K).R, kCombineParts, occ, cap);
+  constexpr int R = combine_shape(K).R;
+  const bool alone = kCombineAlone<K, DT, ODT> &&
+                     (DT != BF16 || ODT != BF16 || a.N / gram_chunk_elems(K, DT) >= 32 * (int64_t)a.B);
+  int64_t grid = a.grid > 0 ? a.grid : stream_grid(a, R, kCombineParts, alone ? 1 : stream_wgs(K, R), occ, cap);
   if (grid > cap) grid = cap;
   if (grid < 1) grid = 1;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), 0, s, rows, a.offsets,

@@ -243,7 +243,7 @@ hipError_t launch_gram_s(const StreamArgs &a, double *partials, hipStream_t s) {
   const int64_t C = gram_chunk_elems(K, DT);
   const int64_t cap = (a.N + C - 1) / C + a.B;
   static const int occ = occupancy(kern);
-  int64_t grid = a.grid > 0 ? a.grid : stream_grid(a, gram_shape(K).R, 1, occ, cap);
+  int64_t grid = a.grid > 0 ? a.grid : stream_grid(a, gram_shape(K).R, 1, stream_wgs(K, gram_shape(K).R), occ, cap);
   if (grid > cap) grid = cap;
   if (grid < 1) grid = 1;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), 0, s, rows, a.offsets,

@@ -304,8 +304,16 @@ constexpr int stream_wgs(int K, int R) {
   const int n = (16 + K * R / 2) / (K * R);
   return n < 2 ? 2 : n;
 }
-inline int64_t stream_grid(const StreamArgs &a, int R, int parts, int occ, int64_t cap) {
-  const int64_t cus = device_cu_count(), few = cus * stream_wgs(a.K, R);
+// The combine of eleven tasks and more, and of ten with bf16 rows and output, is
+// fastest with one: two / one, 2 GiB in ten buckets, us, K=12 bf16 to fp32 532 /
+// 502, K=14 fp32 to bf16 432 / 410, K=16 fp32 469 / 457, K=10 bf16 489 / 462.
+// From bf16 to bf16, where an element costs K fp64 FMAs, only long buckets (32
+// chunks) are: in 600 buckets K=12, 0.7 GiB, 178 / 201, K=16, 2 GiB, 498 / 500.
+template <int K, int DT, int ODT>
+constexpr bool kCombineAlone = K > 10 || (K == 10 && DT == BF16 && ODT == BF16);
+
+inline int64_t stream_grid(const StreamArgs &a, int R, int parts, int wgs, int occ, int64_t cap) {
+  const int64_t cus = device_cu_count(), few = cus * wgs;
   const int64_t chunks = a.N / gram_chunk_elems(a.K, a.dt), B = a.B;
   int64_t grid = cus * occ;
   if (grid > few && chunks * parts >= kLongPass * few && chunks >= (R > 1 ? 3 * B : B / 4)) grid = few;
