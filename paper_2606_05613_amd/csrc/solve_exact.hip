@@ -7,7 +7,7 @@
 // K <= 10, one wavefront per bucket, fp64, in two kernels: the first screens
 // the supports, solves the one or two that can be the answer and leaves a
 // bucket that it is not sure of to the second, which looks at every support
-// (most often none: it then only reads one word a bucket).  Both apply the
+// (most often of no bucket: it then only reads one word each).  Both apply the
 // rules below with the same arithmetic, so the split does not show in the
 // results.
 //
@@ -309,7 +309,7 @@ __device__ __forceinline__ bool before(double f, int slot, double g, int other) 
 // K=10, 6,564 buckets, MGDA 1.19 ms, CAGrad 1.13), though all but one of them
 // fail the answer's conditions by far.  With the screen 0.08 and 0.20 ms, K=8
 // 0.41 -> 0.05, K=4 0.09 -> 0.025; where every bucket is left to the second
-// kernel (K=10, a duplicated task in each) 1.13 -> 1.29.  The screen finds
+// kernel (K=10, a duplicated task in each) 1.14 -> 1.16, K=3 0.054 -> 0.061.  The screen finds
 // that out with one symmetric sweep per support: sweeping task k into the
 // tableau (D G D, D = diag(G_ii^-1/2)) extends the support by k in 55
 // multiply-adds, sweeping it again takes it out, so lane l starts from the
@@ -614,7 +614,13 @@ __global__ __launch_bounds__(kWave, CAGRAD && K == 10 ? 1 : 2) void exact_lanes_
   for (int i = t; i < K * K; i += kWave) {  // D G D (norm: G over it below)
     const double x = S.G[i] / sqrt(S.G[i / K * K + i / K] * S.G[i % K * K + i % K]);
     S.C[i] = x;
-    sure = sure && fabs(x) <= 1.0 + 1e-9;  // (not a NaN)
+    // (not a NaN); two tasks of which one's pivot will be too small after the
+    // other's, as it would be in every support of both: no need to walk them
+    sure = sure && fabs(x) <= 1.0 + 1e-9 && (i % (K + 1) == 0 || x * x <= 1.0 - kScreenPivot);
+  }
+  if (!__all(sure)) {
+    if (t == 0) reinterpret_cast<uint32_t *>(weights)[b * K] = kUnsolved;
+    return;
   }
   WaveSync()();
   Tableau<K, CAGRAD> tb;
@@ -904,13 +910,27 @@ __device__ __forceinline__ void exact_solve_bucket(int K, int64_t b, const doubl
   }
 }
 
-// The buckets that the first kernel left, wavefront by wavefront: lane j looks
-// at bucket blockIdx.x + j * gridDim.x.
-__global__ __launch_bounds__(kWave) void exact_solve_kernel(int K, int B, const double *__restrict__ gram, int method,
-                                                            double c, float *weights, double *__restrict__ aux) {
+// The buckets that the first kernel left (or all of them).  With LOOP a wavefront
+// looks at several, lane j at bucket blockIdx.x + j * gridDim.x, so that a call of
+// very many buckets does not launch one for each just to end it; else one a
+// wavefront, which saves the loop's spills around the support solvers' calls.
+// Loop / one each, us, K=3 CAGrad: 60,000 buckets none of them left 130 / 146, all
+// 673 / 618; 6,564 buckets none 25.5 / 25.2, all 87 / 78; K=10 MGDA, 6,564, all
+// 1,347 / 1,230.
+constexpr int kExactLoopBuckets = 16384;
+template <bool LOOP>
+__global__ __launch_bounds__(kWave) void exact_solve_kernel(int K, int B, int all, const double *__restrict__ gram,
+                                                            int method, double c, float *weights,
+                                                            double *__restrict__ aux) {
+  const uint32_t *mark = reinterpret_cast<const uint32_t *>(weights);
+  if constexpr (!LOOP) {
+    const int64_t b = blockIdx.x;
+    if (all || mark[b * K] == kUnsolved) exact_solve_bucket(K, b, gram, method, c, weights, aux);
+    return;
+  }
   for (int64_t first = blockIdx.x; first < B; first += (int64_t)gridDim.x * kWave) {
     const int64_t mine = first + (int64_t)threadIdx.x * gridDim.x;
-    uint64_t todo = __ballot(mine < B && reinterpret_cast<const uint32_t *>(weights)[mine < B ? mine * K : 0] == kUnsolved);
+    uint64_t todo = __ballot(mine < B && (all || mark[mine < B ? mine * K : 0] == kUnsolved));
     while (todo) {
       const int j = __builtin_ctzll(todo);
       todo &= todo - 1;
@@ -940,12 +960,18 @@ hipError_t launch_lanes(int K, int B, const double *gram, double c, float *weigh
 hipError_t launch_exact_solve(int K, int B, const double *gram, int method, double c, float *weights,
                               double *aux, hipStream_t s) {
   if (K < kMinK || K > kExactMaxK) return hipErrorInvalidValue;
-  const hipError_t e = method == MGDA_EXACT ? launch_lanes<false>(K, B, gram, c, weights, aux, s)
-                                            : launch_lanes<true>(K, B, gram, c, weights, aux, s);
-  if (e != hipSuccess) return e;
-  const int limit = device_cu_count() * 4;  // its wavefronts that fit at a time
-  hipLaunchKernelGGL(exact_solve_kernel, dim3((unsigned)(B < limit ? B : limit)), dim3(kWave), 0, s, K, B, gram,
-                     method, c, weights, aux);
+  const int fit = device_cu_count() * 4;  // wavefronts of the second kernel that fit at a time
+  // two tasks have three supports, which it solves sooner than a screen and
+  // another launch take (613 buckets 10.3 / 12.6 us), as long as all fit
+  const int all = K == 2 && B <= fit;
+  if (!all) {
+    const hipError_t e = method == MGDA_EXACT ? launch_lanes<false>(K, B, gram, c, weights, aux, s)
+                                              : launch_lanes<true>(K, B, gram, c, weights, aux, s);
+    if (e != hipSuccess) return e;
+  }
+  const bool loop = B > kExactLoopBuckets;
+  hipLaunchKernelGGL(loop ? exact_solve_kernel<true> : exact_solve_kernel<false>, dim3((unsigned)(loop ? fit : B)),
+                     dim3(kWave), 0, s, K, B, all, gram, method, c, weights, aux);
   return hipGetLastError();
 }
 
