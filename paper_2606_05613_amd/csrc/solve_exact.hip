@@ -323,10 +323,15 @@ __device__ __forceinline__ bool before(double f, int slot, double g, int other) 
 // entry is below lam), so one test serves both.
 //
 // A support is dropped only if some sign is wrong by more than kScreenTol of
-// the entries' scale, far above the rounding of sweeps whose pivots (the
-// squared distance of task k from the span of those before it, relative to
-// its norm) stay above kScreenPivot, and above the tolerances under which the
-// rules would still keep it.  One or two supports left are solved here;
+// the entries' scale, above the tolerances under which the rules would still
+// keep it.  That this is above the rounding of the sweeps as well, where the
+// pivots (the squared distance of task k from the span of those before it,
+// relative to its norm) stay above kScreenPivot, is measured and not a bound,
+// as chains of nearly dependent tasks have condition numbers up to 1e12 with
+// such pivots: on 20,000 buckets each of such chains, of triangular factors with
+// equal off-diagonal entries, of noise on a low rank, of norms over eight
+// decades and of near ties, every K and both methods, the results are the second
+// kernel's, bit for bit.  One or two supports left are solved here;
 // anything else (more, none, none of them kept, small pivots, a zero or
 // non-finite diagonal, r = 0) leaves a mark in the bucket's first weight, a
 // signalling NaN, which no conversion produces.
@@ -746,19 +751,28 @@ __global__ __launch_bounds__(kWave, CAGRAD && K == 10 ? 1 : 2) void exact_lanes_
       bf = S.bvec[t] + rr * sqrt(gtt > 0.0 ? gtt : 0.0);
       bslot = t;
     }
+    bool some = false;  // a support left is a vertex, or one of its points is kept
     for (int i = 0; i < n; ++i) {
       const uint32_t m = (uint32_t)__builtin_amdgcn_readfirstlane((int)left[i]);
-      if (__builtin_popcount(m) < 2) continue;
+      if (__builtin_popcount(m) < 2) {
+        some = true;
+        continue;
+      }
       double w[K], f;
       const bool kept = lane_cagrad_support<K>(S.G, S.bvec, rr, m, t, w, &f);
       if (kept && t < 2) {
 #pragma unroll
         for (int u = 0; u < K; ++u) S.C[(2 * i + t) * K + u] = w[u];
       }
+      some = __any(kept) || some;
       if (kept && before(f, K + 2 * i + (t & 1), bf, bslot)) {
         bf = f;
         bslot = K + 2 * i + (t & 1);
       }
+    }
+    if (!some) {
+      if (t == 0) reinterpret_cast<uint32_t *>(weights)[b * K] = kUnsolved;
+      return;
     }
 #pragma unroll
     for (int off = kWave / 2; off >= 1; off >>= 1) {

@@ -144,3 +144,50 @@ def test_exact_never_takes_the_cooperative_path(gpu_lib):
             assert gpu_lib.resolve_path(g, 3, method=m, max_iter=0) == gpu_lib.PATH_TWO_PASS
     finally:
         gpu_lib.set_resolve_path(0)
+
+
+def _ill_conditioned(kind, k, nb, rng):
+    """Gram matrices with pivots around the least that the screen trusts: chains
+    of nearly dependent tasks, triangular factors with equal off-diagonal
+    entries, noise on a low rank, norms over eight decades."""
+    n = 4 * k
+    if kind == "chain":
+        x = np.empty((nb, k, n))
+        x[:, 0] = rng.standard_normal((nb, n))
+        eps = 10.0 ** rng.uniform(-3.2, -0.5, (nb, k, 1))
+        for i in range(1, k):
+            x[:, i] = x[:, i - 1] + eps[:, i] * rng.standard_normal((nb, n))
+    elif kind == "triangular":
+        th = rng.uniform(0.02, 1.2, (nb, 1, 1))
+        r = np.eye(k)[None] - np.cos(th) * np.triu(np.ones((k, k)), 1)[None]
+        r = r * np.maximum(np.sin(th) ** np.arange(k)[None, :, None], 1e-2)
+        x = np.swapaxes(r, 1, 2) * (1 + 1e-3 * rng.standard_normal((nb, k, k)))
+        x = np.take_along_axis(x, np.argsort(rng.random((nb, k)), axis=1)[:, :, None], 1)
+    elif kind == "low rank":
+        r = max(1, k // 2)
+        x = rng.standard_normal((nb, k, r)) @ rng.standard_normal((nb, r, n))
+        x += 10.0 ** rng.uniform(-3.5, -1, (nb, 1, 1)) * rng.standard_normal((nb, k, n))
+    else:
+        x = rng.standard_normal((nb, k, n)) + 0.5 * rng.standard_normal((nb, 1, n))
+        x *= 10.0 ** rng.uniform(-4, 4, (nb, k, 1))
+    return x @ np.swapaxes(x, 1, 2)
+
+
+@pytest.mark.parametrize("method,scale", [("mgda-exact", 2.0 ** 700), ("cagrad-exact", 2.0 ** -700)])
+@pytest.mark.parametrize("K", [2, 3, 6, 7, 10])
+def test_screen_does_not_show(gpu_lib, K, method, scale):
+    """The same buckets scaled by an even power of two (its root is one as well)
+    are out of the range that the screen takes on, so the second kernel solves
+    them all; every number of its arithmetic scales exactly, and with it the
+    result: the same bits as with the screen."""
+    rng = np.random.default_rng(4200 + K)
+    for kind in ("chain", "triangular", "low rank", "norms"):
+        print(f"case screen {method} K={K} {kind}", flush=True)
+        G = _ill_conditioned(kind, K, 2000, rng)
+        G[::50] = _grams(K, 40, 4300 + K)  # singular ones among them
+        G = torch.from_numpy(np.ascontiguousarray(G)).cuda()
+        for c in (0.1, 0.5):
+            W, A = gpu_lib.solve(G, method, cagrad_c=c)
+            W2, A2 = gpu_lib.solve(G * scale, method, cagrad_c=c)
+            same = (W.view(torch.int32) == W2.view(torch.int32)).all(1) & (A.view(torch.int64) == A2.view(torch.int64)).all(1)
+            assert bool(same.all()), f"{kind} c={c}: buckets {torch.nonzero(~same).flatten()[:5].tolist()}"
