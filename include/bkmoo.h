@@ -251,7 +251,12 @@ bkmoo_status bkmoo_combine(int32_t K, const void *const *grads, bkmoo_dtype dt, 
  * least 10% stays on chip, averaging (all K rows) at least max(24, 6 K) MiB
  * plus 4 MiB per us of L; refill (K <= 10) for at least 8 buckets whose
  * round of G buckets holds at least 64 + 2 L MiB and, for G > 1, at most
- * 300 MiB (a round the Infinity Cache still serves).  Hybrid where it
+ * 300 MiB (a round the Infinity Cache still serves), except that for K >= 7
+ * and at most 256 MiB of gradients in all the two passes run instead where
+ * the average bucket, rounded up to whole Gram chunks of 16,384 (f32) or
+ * 32,768 (bf16) elements, makes no more chunks in all than the device has
+ * CUs (bf16: 1.4 times as many at K = 7, twice as many above), or where the
+ * buckets fill at most 60% of ceil(B / G) rounds of G.  Hybrid where it
  * is eligible, except refill for K = 3 and for K <= 4 with L >= 4 us; else
  * refill where eligible; else the two passes.  Exact solvers never take a cooperative
  * path.

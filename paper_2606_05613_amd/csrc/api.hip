@@ -330,21 +330,41 @@ constexpr double kRefillOverHybridUs = 4.0;
 // Gradients that the last-level cache holds are read a second time from there,
 // and three ordinary launches have no gaps of ~10 us around them as a
 // cooperative one has: with many tasks, of which the refill kernel keeps the
-// smaller share on chip, the two passes win there.  13 / 31 buckets, inputs
-// new to the caches, us, refill / two passes: K=8 bf16 PCGrad 90 MiB 71 / 52,
-// 130 MiB 86 / 74 and 84 / 80, 200 MiB 124 / 95, 300 MiB 144 / 141 and 140 / 141, 450 MiB 183 /
-// 201 and 192 / 195 (MGDA alike); K=10 fp32 MGDA 130 MiB 86 / 69, 200 MiB 119 /
-// 116, 300 MiB 147 / 139 and 133 / 139.  With fewer tasks there is no such
-// line: K=4 bf16 65 / 55, 78 / 78, 121 / 102, K=4 fp32 75 / 85 and 103 / 109,
-// K=3 83 / 88 and 129 / 114, K=2 fp32 58 / 63 and 74 / 79 at 90 to 200 MiB.
+// smaller share on chip, the two passes win there.  How far depends on how many
+// of the Gram pass's chunks a CU gets: time goes up in steps, at one and at two a
+// CU (256, 512 chunks).  Two passes / refill, 9, 14, 31 and 60 buckets, PCGrad,
+// inputs new to the caches:
+//   up to 256 chunks  K=7 fp32 0.77-1.04, K=8 fp32 0.68-1.00, K=10 fp32 0.67-1.05,
+//                     K=7 bf16 0.70-0.97, K=8 bf16 0.59-0.92, K=10 bf16 0.59-0.91
+//   to 512 chunks     K=7 fp32 0.86-1.31, K=8 fp32 0.76-1.20, K=10 fp32 0.81-1.14,
+//                     K=8 bf16 0.66-0.99, K=9 bf16 0.70-1.03, K=10 bf16 0.64-0.94;
+//                     K=7 bf16 to 360 chunks 0.92-0.99, beyond 0.78-1.15
+//   to 700 chunks     K=7 and K=8 fp32 1.01-1.35, bf16 0.94-1.19
+// (MGDA and CAGrad with 5 to 20 iterations within 0.05 of that, in favour of the
+// two passes as iterations go up).  Below 0.85 in the second row are calls whose
+// buckets leave the refill kernel's last round mostly empty (9 buckets in groups
+// of 8).  With fewer tasks there is no such line: K=4 bf16 65 / 55, 78 / 78, 121 /
+// 102 us (refill / two passes), K=4 fp32 75 / 85 and 103 / 109, K=3 83 / 88 and 129
+// / 114, K=2 fp32 58 / 63 and 74 / 79 at 90 to 200 MiB.
 constexpr int kSmallMinK = 7;
 constexpr double kSmallMiB = 256.0;
+constexpr double kSmallEmptyRound = 0.6;  // share of the rounds' places that buckets take
 
 int refill_groups(int K, int dt, int64_t N, int B) {
   const double bucket_mib = (double)N / B * K * elem_bytes(dt) / (1 << 20);
   int g = (int)(kRefillRoundMiB / (bucket_mib > 1e-9 ? bucket_mib : 1e-9) + 0.5);
   g = g < 1 ? 1 : g > kRefMaxGroups ? kRefMaxGroups : g;
   return g < B ? g : (B > 0 ? B : 1);
+}
+
+// Whether a call of many tasks is short enough for the two passes (above).
+bool two_passes_win(int K, int dt, int64_t N, int B, int groups) {
+  if (K < kSmallMinK || (double)N * K * elem_bytes(dt) > kSmallMiB * (1 << 20)) return false;
+  const int64_t C = gram_chunk_elems(K, dt), cus = device_cu_count();
+  const int64_t chunks = B * ((N / B + C - 1) / C);  // of B equal buckets
+  const double per_cu = dt != BF16 ? 1.0 : K == 7 ? 1.4 : 2.0;
+  const int rounds = (B + groups - 1) / groups;
+  return (double)chunks <= per_cu * (double)cus || B <= kSmallEmptyRound * groups * rounds;
 }
 
 // Workgroups for the single-buffer pipelined path if it can run and, unless
@@ -363,7 +383,7 @@ int choose_refill(int K, int dt, int out_dt, int64_t N, int B, bool vec, int met
     return 0;
   if (mode == BKMOO_PATH_REFILL) return g;
   if (B < kHybridMinBuckets) return 0;
-  if (K >= kSmallMinK && (double)N * K * elem_bytes(dt) <= kSmallMiB * (1 << 20)) return 0;
+  if (two_passes_win(K, dt, N, B, groups)) return 0;
   const double round_mib = (double)N / B * K * elem_bytes(dt) / (1 << 20) * groups;
   const double min_mib = kRefillMinRoundMiB + kRefillMiBPerUs * solve_latency_us(method, K, iters);
   return round_mib >= min_mib && (round_mib <= kRefillMaxRoundMiB || groups == 1) ? g : 0;

@@ -154,12 +154,21 @@ def test_forced_hybrid_and_unknown_paths(gpu_lib, rows_4x2g):
             gpu_lib.set_resolve_path(bad)
 
 
-@pytest.mark.parametrize("K,mib,want", [(8, 104, "two-pass"), (8, 250, "two-pass"), (8, 264, "refill"),
-                                        (7, 104, "two-pass"), (6, 104, "refill"), (10, 200, "two-pass")])
-def test_small_calls_of_many_tasks_take_the_two_passes(gpu_lib, K, mib, want):
-    """Seven tasks and more, at most 256 MiB of gradients in all (13 buckets):
-    the two passes; beyond, or with fewer tasks, the refill kernel."""
+@pytest.mark.parametrize("dtype,K,mib,B,want", [
+    ("bf16", 8, 104, 13, "two-pass"), ("bf16", 8, 250, 13, "two-pass"), ("bf16", 8, 264, 13, "refill"),
+    ("bf16", 7, 104, 13, "two-pass"), ("bf16", 6, 104, 13, "refill"), ("bf16", 10, 200, 13, "two-pass"),
+    # at most one Gram chunk a CU with fp32 rows, 1.4 or (K >= 8) two with bf16
+    ("f32", 8, 120, 12, "two-pass"), ("f32", 8, 132, 12, "refill"), ("f32", 7, 250, 13, "refill"),
+    ("f32", 10, 180, 31, "refill"), ("bf16", 7, 150, 13, "two-pass"), ("bf16", 7, 250, 13, "refill"),
+    ("bf16", 8, 252, 60, "refill"),
+    # unless the refill kernel's groups of buckets leave most of its last round empty
+    ("f32", 8, 204, 9, "two-pass"), ("bf16", 7, 216, 9, "two-pass")])
+def test_small_calls_of_many_tasks_take_the_two_passes(gpu_lib, dtype, K, mib, B, want):
+    """Seven tasks and more, at most 256 MiB of gradients in all, and few enough
+    chunks for the chip's CUs: the two passes; beyond, or with fewer tasks, the
+    refill kernel."""
     names = {gpu_lib.PATH_TWO_PASS: "two-pass", gpu_lib.PATH_HYBRID: "hybrid", gpu_lib.PATH_REFILL: "refill"}
-    g = torch.empty((K, (mib * MIB // (2 * K)) // 8 * 8), dtype=torch.bfloat16, device="cuda")
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.empty((K, (mib * MIB // (dt.itemsize * K)) // 8 * 8), dtype=dt, device="cuda")
     gpu_lib.set_resolve_path(0)
-    assert names[gpu_lib.resolve_path(g, 14, "pcgrad", 0)] == want
+    assert names[gpu_lib.resolve_path(g, B + 1, "pcgrad", 0)] == want
