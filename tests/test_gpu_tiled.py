@@ -80,3 +80,25 @@ def test_form_follows_the_offsets(gpu_lib, count, uneven):
     gpu_lib.resolve(x, torch.from_numpy(offs).cuda(), "cagrad", workspace=ws)
     assert gpu_lib.read_device_error(ws) & gpu_lib.DEVERR_OFFSETS
     assert int(ws[:8].view(torch.int32)[TILED_WORD]) == 0
+
+
+@pytest.mark.parametrize("K,dtype", [(2, "f32"), (3, "bf16")])
+def test_one_large_bucket_of_many_keeps_the_pipelined_form(gpu_lib, K, dtype):
+    """2.4 GiB in 40 buckets, one of a third of it: the others' groups end early,
+    but the pipelined form still reads less."""
+    item = 4 if dtype == "f32" else 2
+    n = 2500 * (1 << 20) // (K * item) // 8 * 8
+    w = np.ones(40)
+    w[13] = 20
+    offs = (np.concatenate([[0], np.cumsum(w)]) / w.sum() * n).astype(np.int64)
+    offs[-1] = n
+    x = torch.ones((K, n), dtype=torch.float32 if dtype == "f32" else torch.bfloat16, device="cuda")
+    gpu_lib.set_resolve_path(0)
+    print(f"case tiled or not K={K} {dtype} n={n}", flush=True)
+    assert gpu_lib.resolve_path(x, 41, "cagrad", 20) == gpu_lib.PATH_REFILL
+    ws = torch.empty(gpu_lib.workspace_size(K, n, 40, x.dtype), dtype=torch.uint8, device="cuda")
+    gpu_lib.resolve(x, torch.from_numpy(offs).cuda(), "cagrad", workspace=ws)
+    assert gpu_lib.read_device_error(ws) == 0
+    assert int(ws[:8].view(torch.int32)[TILED_WORD]) == 0
+    # the host's byte count takes the same form: some bytes are read once
+    assert gpu_lib.resolve_traffic(K, offs, dtype, gpu_lib.PATH_REFILL, method="cagrad") < (2 * K + 1) * item * n
