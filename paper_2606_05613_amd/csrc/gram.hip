@@ -101,8 +101,8 @@ __global__ __launch_bounds__(kThreads) void gram_mfma_kernel(Rows<K> rows, const
   constexpr int64_t C = gram_chunk_elems(K, BF16);
   constexpr int P = pairs(K), V = vec_elems(BF16), S = 16 / K;
   constexpr int kWaves = kThreads / kWave, kStep = 4 * S;  // vectors of a row in a product
-  constexpr int kSteps = kWave / kStep;                    // whole products in a tile (S = 3: 60 of 64 vectors)
-  constexpr int kTile = kSteps * kStep;                    // vectors of a row in a tile
+  constexpr int kSteps = kWave / kStep;                    // products in a tile (a vector of every row a lane)
+  static_assert(K >= kMfmaMinK && kSteps * kStep == kWave, "one or two slices");
   __shared__ u32x4 tile[kWaves][K * kRowPitch];
   __shared__ double red[2][kWaves * S][P];
 
@@ -145,19 +145,19 @@ __global__ __launch_bounds__(kThreads) void gram_mfma_kernel(Rows<K> rows, const
     u32x4 q[K];
     const auto load = [&](int v0) {
       const int v = v0 + lane;
-      const bool in = lane < kTile && v < sp.nv;
+      const bool in = v < sp.nv;
 #pragma unroll
       for (int i = 0; i < K; ++i) {
         q[i] = u32x4{0u, 0u, 0u, 0u};
         if (in) q[i] = stream_load(static_cast<const uint16_t *>(rows.p[i]) + sp.lo_a, v);
       }
     };
-    int v0 = wave * kTile;
+    int v0 = wave * kWave;
     if (v0 < sp.nv) load(v0);
-    for (; v0 < sp.nv; v0 += kWaves * kTile) {
+    for (; v0 < sp.nv; v0 += kWaves * kWave) {
 #pragma unroll
       for (int i = 0; i < K; ++i) own[i * kRowPitch + lane] = q[i];
-      if (v0 + kWaves * kTile < sp.nv) load(v0 + kWaves * kTile);
+      if (v0 + kWaves * kWave < sp.nv) load(v0 + kWaves * kWave);
       // one wavefront's LDS accesses are executed in order: the compiler must
       // only keep them so
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");

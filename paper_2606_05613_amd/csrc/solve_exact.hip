@@ -407,38 +407,38 @@ __device__ __forceinline__ bool lane_ge_solve(double (&A)[NM], double (&z)[M], i
 #pragma unroll
   for (int k = 0; k < NM; ++k) {
     if (k < n) {
-    double v = t >= k && t < n ? -fabs(A[k]) : 1.0;  // least = largest magnitude, lowest row first
-    int p = t;
-    argmin_step<kDppXor1>(v, p);
-    argmin_step<kDppXor2>(v, p);
-    argmin_step<kDppRor4>(v, p);
-    argmin_step<kDppRor8>(v, p);
-    p = __builtin_amdgcn_readfirstlane(p);
-    const bool zero = lane_f64(v, 0) == 0.0;
-    ok = ok && !zero;
-    if (p != k) {
+      double v = t >= k && t < n ? -fabs(A[k]) : 1.0;  // least = largest magnitude, lowest row first
+      int p = t;
+      argmin_step<kDppXor1>(v, p);
+      argmin_step<kDppXor2>(v, p);
+      argmin_step<kDppRor4>(v, p);
+      argmin_step<kDppRor8>(v, p);
+      p = __builtin_amdgcn_readfirstlane(p);
+      const bool zero = lane_f64(v, 0) == 0.0;
+      ok = ok && !zero;
+      if (p != k) {
 #pragma unroll
-      for (int c = k; c < NM; ++c) {
-        const double a = lane_f64(A[c], k), b = lane_f64(A[c], p);
-        A[c] = t == k ? b : t == p ? a : A[c];
+        for (int c = k; c < NM; ++c) {
+          const double a = lane_f64(A[c], k), b = lane_f64(A[c], p);
+          A[c] = t == k ? b : t == p ? a : A[c];
+        }
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+          const double a = lane_f64(z[j], k), b = lane_f64(z[j], p);
+          z[j] = t == k ? b : t == p ? a : z[j];
+        }
+      }
+      const double f = A[k] / (zero ? 1.0 : lane_f64(A[k], k));
+#pragma unroll
+      for (int c = k + 1; c < NM; ++c) {
+        const double y = f * lane_f64(A[c], k);
+        A[c] = t > k ? A[c] - y : A[c];
       }
 #pragma unroll
       for (int j = 0; j < M; ++j) {
-        const double a = lane_f64(z[j], k), b = lane_f64(z[j], p);
-        z[j] = t == k ? b : t == p ? a : z[j];
+        const double y = f * lane_f64(z[j], k);
+        z[j] = t > k ? z[j] - y : z[j];
       }
-    }
-    const double f = A[k] / (zero ? 1.0 : lane_f64(A[k], k));
-#pragma unroll
-    for (int c = k + 1; c < NM; ++c) {
-      const double y = f * lane_f64(A[c], k);
-      A[c] = t > k ? A[c] - y : A[c];
-    }
-#pragma unroll
-    for (int j = 0; j < M; ++j) {
-      const double y = f * lane_f64(z[j], k);
-      z[j] = t > k ? z[j] - y : z[j];
-    }
     }
   }
 #pragma unroll

@@ -247,7 +247,7 @@ __device__ void solve_cagrad(Shared &S, int K, int iters, double c, int t) {
 
 // ---- lane-parallel solvers for a compile-time K <= 16 ---------------------
 // The same algorithms as solve_mgda and solve_cagrad above (same start,
-// steps, tie rules, line searches and fixed iteration counts), run by one
+// steps, tie rules, line searches, iteration counts and early end), run by one
 // whole wavefront with lane i < K holding task i's row of G, its entry of
 // G a and its variable, so a step costs O(K) instead of O(K^2) arithmetic
 // per lane.  Cross-lane steps use DPP within the first row of 16 lanes

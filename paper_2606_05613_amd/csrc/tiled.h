@@ -21,7 +21,10 @@
 // No cycle of waits: the weights of window w need every workgroup's arrivals
 // up to window w, and a workgroup arrives for window w + 1 before its first
 // wait for window w; solvers wait only for arrivals, bucket by bucket upwards.
-// The Gram sums are those of the Gram pass's chunks, whatever the grid.
+// The Gram sums are made chunk by chunk, with the Gram pass's chunks, so they do
+// not depend on the grid.  They are not that pass's bits: the solver adds a
+// bucket's slots in an order of its own, and bf16 rows of seven tasks and more go
+// through FMAs here and through the matrix cores there.
 #pragma once
 
 #include "chunk.h"
