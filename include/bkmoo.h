@@ -49,7 +49,10 @@
  *   - Inputs are converted exactly to fp32; inner products accumulate in fp32
  *     per lane and in fp64 across lanes, waves and chunks, in a fixed order:
  *     results are bitwise reproducible for identical inputs on the same
- *     device model, independent of the launch grid.
+ *     device model, independent of the launch grid.  In bkmoo_gram and the
+ *     two-pass bkmoo_resolve the order of a bucket's sum follows from the
+ *     bucket's length and its start's 16-byte phase alone, whatever else the
+ *     call holds.
  *   - Non-finite inputs propagate (a NaN in a bucket makes its Gram, weights
  *     and update NaN); nothing is filtered.
  *   - Synchronous argument errors are returned before anything is queued.
@@ -111,8 +114,9 @@ typedef enum {
 
 /* Hyper-parameters of the solve step (host struct). */
 typedef struct {
-  /* Frank-Wolfe iterations for MGDA and CAGrad (fixed count, no early
-   * exit), >= 0.  The usual value is 20. */
+  /* Frank-Wolfe iterations for MGDA and CAGrad, >= 0; the usual value is 20.
+   * A step that leaves the point where it is ends them early: every later
+   * one would leave it there too, so the result is that of all of them. */
   int32_t max_iter;
   /* CAGrad conflict-aversion c in [0, 1): the update stays within
    * c * ||mean gradient|| of the mean gradient (Eq. cagrad); Appendix E
@@ -218,7 +222,7 @@ bkmoo_status bkmoo_combine(int32_t K, const void *const *grads, bkmoo_dtype dt, 
  * synchronisation.  gram, weights and aux may be NULL, in which case the
  * intermediate values live in the workspace only.
  *
- * Two implementations, same definitions and tolerances:
+ * Three implementations, same definitions and tolerances:
  *   two-pass  the kernels of bkmoo_gram, bkmoo_solve and bkmoo_combine;
  *             results equal those three calls bitwise.
  *   hybrid    (K <= 8, 16-byte-phase-aligned rows and output) one
@@ -244,7 +248,14 @@ bkmoo_status bkmoo_combine(int32_t K, const void *const *grads, bkmoo_dtype dt, 
  *             size, all rows), 1, 32), at most B) and group g takes buckets
  *             g, g+G, ..., so small buckets hide their hand-off too.
  *             Rounding, determinism and bounded waits as for hybrid (its
- *             segments also depend on G).
+ *             segments also depend on G).  Where bucket lengths differ so
+ *             much that one group would outlast the others, the device
+ *             selects, from the offsets, the kernel's tiled form instead: it
+ *             spreads every bucket over all data workgroups in chunks and
+ *             reads everything twice.  Its Gram sums are made per chunk, in
+ *             another fixed order again (not dependent on the CU count).  Only
+ *             the automatic choice selects it; bkmoo_set_resolve_path(
+ *             BKMOO_PATH_REFILL) always runs the other form.
  * Automatic choice, with L the estimated solve latency (0.07 K us per MGDA
  * iteration, 0.22 K us per CAGrad iteration, 0.1 K^2 us for PCGrad, 0 for
  * the mean): hybrid (K <= 8) is eligible for at least 8 buckets of which at
@@ -372,8 +383,11 @@ bkmoo_status bkmoo_conflicts(int32_t K, int32_t B, const double *gram, double *c
  *   BKMOO_PATH_TWO_PASS  2*K*s*N + s_out*N
  *   BKMOO_PATH_HYBRID    K*s*N + s_out*N, plus K*s per element a data
  *                        workgroup did not keep on chip (read twice)
- * with s, s_out the input and output element sizes; BKMOO_PATH_REFILL as
- *                        BKMOO_PATH_HYBRID with its own (larger) kept share.  The small per-bucket
+ *   BKMOO_PATH_REFILL    as BKMOO_PATH_HYBRID with its own (larger) kept
+ *                        share; where the tiled form would run for these
+ *                        offsets (no path being forced), as
+ *                        BKMOO_PATH_TWO_PASS
+ * with s, s_out the input and output element sizes.  The small per-bucket
  * terms (offsets, Gram matrices, weights, partial sums) are left out.  The
  * hybrid path depends on the current device's CU count, and its segments
  * also on the method and iteration count (`method`,

@@ -392,7 +392,8 @@ def resolve_traffic(K: int, bucket_offsets, dtype, path: int, out_dtype=None, me
                     max_iter: int = 20) -> int:
     """Bytes a resolve on `path` requests from memory for these offsets (a
     host int64 array-like of B+1 entries); on the hybrid path part of the
-    re-read is served by the last-level cache."""
+    re-read is served by the last-level cache, and on the refill path uneven
+    offsets may select its tiled form, which reads everything twice."""
     import numpy as np
     offs = np.ascontiguousarray(np.asarray(bucket_offsets, dtype=np.int64))
     code = lambda d: d if isinstance(d, int) else (F32 if d in (torch.float32, "f32") else BF16)
