@@ -118,8 +118,8 @@ bool k_unsupported(int K, int method) { return K > kMaxK || (is_exact(method) &&
 hipError_t schedule_pass(const int64_t *offsets, int B, int64_t N, int K, int dt, int64_t *chunk_start,
                          int64_t *group_start, int64_t *part_start, uint32_t *err, hipStream_t s) {
   if (B <= kSelfBuckets) return hipSuccess;
-  return launch_schedule(offsets, B, N, gram_chunk_elems(K, dt), chunk_start, group_start, part_start, err, nullptr,
-                         0, PipePlan{}, s);
+  return launch_schedule(offsets, B, N, gram_chunk_elems(K, dt), sum_direct(pairs(K)), chunk_start, group_start,
+                         part_start, err, nullptr, 0, PipePlan{}, s);
 }
 
 bkmoo_status hip_status(hipError_t e) { return e == hipSuccess ? BKMOO_OK : BKMOO_EHIP; }
@@ -327,10 +327,9 @@ constexpr double kRefillMinRoundMiB = 64.0, kRefillMiBPerUs = 2.0;
 // CAGrad 5.49 / 5.04: at K = 3 the refill kernel wins for every method.
 constexpr double kRefillOverHybridUs = 4.0;
 
-// Gradients that the last-level cache holds are read a second time from there,
-// and three ordinary launches have no gaps of ~10 us around them as a
-// cooperative one has: with many tasks, of which the refill kernel keeps the
-// smaller share on chip, the two passes win there.  How far depends on how many
+// Three ordinary launches have no gaps of ~10 us around them as a cooperative one
+// has, so short calls of many tasks, of which the refill kernel keeps the smaller
+// share on chip, are faster on the two passes.  How far depends on how many
 // of the Gram pass's chunks a CU gets: time goes up in steps, at one and at two a
 // CU (256, 512 chunks).  Two passes / refill, 9, 14, 31 and 60 buckets, PCGrad,
 // inputs new to the caches:
@@ -587,7 +586,7 @@ bkmoo_status resolve_impl(int32_t K, const void *const *grads, bkmoo_dtype dt, i
     const PipePlan plan = path == BKMOO_PATH_REFILL && g_resolve_path.load() == 0
                               ? pipe_plan(K, (int)dt, (int)out_dt, (int)method, iters, groups)
                               : PipePlan{};
-    hipError_t e = launch_schedule(bucket_offsets, B, N, gram_chunk_elems(K, dt), w.chunk_start, nullptr, nullptr,
+    hipError_t e = launch_schedule(bucket_offsets, B, N, gram_chunk_elems(K, dt), 0, w.chunk_start, nullptr, nullptr,
                                    w.err, w.sync, (1 + kFlagCopies) * (int64_t)B * kSyncStride, plan, stream);
     if (e != hipSuccess) return BKMOO_EHIP;
     uint32_t *flags = w.sync + (int64_t)B * kSyncStride;

@@ -37,7 +37,7 @@ __global__ __launch_bounds__(kThreads) void combine_kernel(
 
   __shared__ int64_t lps[SELF ? kSelfBuckets + 1 : 1];
   if constexpr (SELF) {
-    if (!own_schedule<true>(offs, B, C * kCombineParts, sched, lps)) return;
+    if (!own_schedule<true>(offs, B, C * kCombineParts, sum_direct(pairs(K)), sched, lps)) return;
   }
   const int64_t *ps = SELF ? lps : gps;
   const int64_t total = ps[B];

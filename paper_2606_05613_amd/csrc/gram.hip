@@ -37,7 +37,7 @@ __global__ __launch_bounds__(kThreads) void gram_partial_kernel(
 
   __shared__ int64_t lcs[SELF ? kSelfBuckets + 1 : 1];
   if constexpr (SELF) {
-    if (!own_schedule<false>(offs, B, C, sched, lcs)) return;
+    if (!own_schedule<false>(offs, B, C, sum_direct(P), sched, lcs)) return;
   }
   const int64_t *cs = SELF ? lcs : gcs;
   int64_t c, cend;
@@ -108,7 +108,7 @@ __global__ __launch_bounds__(kThreads) void gram_mfma_kernel(Rows<K> rows, const
 
   __shared__ int64_t lcs[SELF ? kSelfBuckets + 1 : 1];
   if constexpr (SELF) {
-    if (!own_schedule<false>(offs, B, C, sched, lcs)) return;
+    if (!own_schedule<false>(offs, B, C, sum_direct(P), sched, lcs)) return;
   }
   const int64_t *cs = SELF ? lcs : gcs;
   int64_t c, cend;
@@ -190,7 +190,7 @@ __global__ __launch_bounds__(kThreads) void gram_mfma_kernel(Rows<K> rows, const
   }
 }
 
-// Finalize, level 1 (only buckets of kSumDirect chunks and more): one workgroup
+// Finalize, level 1 (only buckets of sum_direct chunks and more): one workgroup
 // per group of up to kFinalizeGroup consecutive chunks of one bucket
 // (grid-stride over the groups) leaves the group's sum in the slot of the
 // group's first chunk, which only this workgroup reads.
@@ -285,8 +285,9 @@ hipError_t launch_gram_partials(const StreamArgs &a, double *partials, hipStream
   hipError_t e = a.dt == F32 ? dispatch_gram<F32>(a, partials, s) : dispatch_gram<BF16>(a, partials, s);
   // the chunks that one bucket can have, and the groups of all that have them
   const int64_t chunks = (a.N + gram_chunk_elems(a.K, a.dt) - 1) / gram_chunk_elems(a.K, a.dt);
-  if (e != hipSuccess || chunks < kSumDirect) return e;
-  const int64_t groups = chunks / kFinalizeGroup + chunks / kSumDirect;
+  const int64_t direct = sum_direct(pairs(a.K));
+  if (e != hipSuccess || chunks < direct) return e;
+  const int64_t groups = chunks / kFinalizeGroup + chunks / direct;
   const int64_t limit = (int64_t)device_cu_count() * 4;
   hipLaunchKernelGGL(gram_group_kernel, dim3((unsigned)(groups < limit ? groups : limit)), dim3(kSumThreads), 0, s,
                      pairs(a.K), a.B, a.chunk_start, a.group_start, partials);

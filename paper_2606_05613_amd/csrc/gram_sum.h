@@ -8,12 +8,7 @@ namespace bkmoo {
 
 namespace {
 
-// Threads that add up a bucket's slots side by side: at K = 16 (136 pairs)
-// three rows of them.
-constexpr int kSumThreads = 512;
-static_assert(kSumThreads >= pairs(kMaxK), "a thread per pair");
-
-// The workgroup that does: a thread each, or one wavefront for all of them (the
+// The workgroup that adds up a bucket's slots: a thread each (kSumThreads), or one wavefront for all of them (the
 // same sums in the same order) where a call has many buckets of few slots, of
 // which most threads would only start and end: from four buckets a CU on and up
 // to four chunks a bucket on average.  The Gram call, us, threads / wavefront:
@@ -66,12 +61,12 @@ __device__ __forceinline__ double sum_slots(const double *__restrict__ slots, in
   return s;
 }
 
-// Pair p's sum over bucket b, of its chunk slots or, in a bucket of kSumDirect
+// Pair p's sum over bucket b, of its chunk slots or, in a bucket of sum_direct
 // chunks and more, of its group sums.
 template <int T>
 __device__ __forceinline__ double sum_bucket(const double *__restrict__ partials, const int64_t *__restrict__ cs,
                                              int64_t b, int P, double *red) {
-  const int64_t c0 = cs[b], n = cs[b + 1] - c0, step = n < kSumDirect ? 1 : kFinalizeGroup;
+  const int64_t c0 = cs[b], n = cs[b + 1] - c0, step = n < sum_direct(P) ? 1 : kFinalizeGroup;
   return sum_slots<T>(partials, c0, (n + step - 1) / step, step, P, red);
 }
 

@@ -58,17 +58,28 @@ static_assert(combine_parts_fit(), "a Gram chunk is kCombineParts combine chunks
 
 constexpr int pairs(int K) { return K * (K + 1) / 2; }
 
-// The Gram finalize adds the chunk slots of a bucket of fewer than kSumDirect
-// chunks directly, one workgroup per bucket; in a longer bucket groups of this
-// many consecutive chunks come first (one workgroup per group, so that a
-// single large bucket is not added by one), then the group sums.  Groups of
+// Threads that add up a bucket's slots side by side in the Gram finalize: at
+// K = 16 (136 pairs) three rows of them.
+constexpr int kSumThreads = 512;
+static_assert(kSumThreads >= pairs(kMaxK), "a thread per pair");
+
+// The Gram finalize adds the chunk slots of a bucket of fewer than sum_direct
+// chunks directly, one workgroup per bucket; in a longer bucket groups of
+// kFinalizeGroup consecutive chunks come first (one workgroup per group, so that
+// a single large bucket is not added by one), then the group sums.  Groups of
 // 64 fill the chip sooner than the 1024 used before: K=8 bf16, one bucket of
 // 124M elements (3,798 chunks), 40 + 5 us for the two kernels with 1024.
-// Which of the two it is depends on the bucket alone, so its matrix is the same
-// bits whatever else the call holds; and short buckets have no groups (K=2 fp32,
-// 20,000 buckets of one chunk, a group each: 209 us for the group kernel).
+// Which of the two it is depends on the bucket (and K) alone, so its matrix is the
+// same bits whatever else the call holds; and short buckets have no groups (K=2
+// fp32, 20,000 buckets of one chunk, a group each: 209 us for the group kernel).
+// The line, 64 slots a thread: groups save (or cost) us, ten buckets, K=16 at 190
+// chunks -0.6, 260 1.4, 400 6.5; K=12 260 -1.0, 400 1.3; K=10 260 -1.0, 400 1.5;
+// K=8 505 -0.4; K=4 and K=2 505 -2.4 and -3.6.
 constexpr int kFinalizeGroup = 64;
-constexpr int64_t kSumDirect = 512;
+constexpr int64_t kMaxSumDirect = 512;
+__host__ __device__ constexpr int64_t sum_direct(int P) {
+  return kSumThreads / P * kFinalizeGroup < kMaxSumDirect ? kSumThreads / P * kFinalizeGroup : kMaxSumDirect;
+}
 // Size of a finalize group in the workspace's layout (see Layout::part_start).
 constexpr int kLayoutGroup = 1024;
 
@@ -195,8 +206,8 @@ struct StreamArgs {
 // Validates offsets, writes chunk_start for chunks of C elements (and, where
 // they are not null, the prefixes of finalize groups and of combine parts),
 // sets the error word and, by `plan`, the word after it, and zeroes `nsync`
-// words at `sync`.
-hipError_t launch_schedule(const int64_t *offsets, int B, int64_t N, int64_t C, int64_t *chunk_start,
+// words at `sync`.  direct: sum_direct.
+hipError_t launch_schedule(const int64_t *offsets, int B, int64_t N, int64_t C, int64_t direct, int64_t *chunk_start,
                            int64_t *group_start, int64_t *part_start, uint32_t *err, uint32_t *sync, int64_t nsync,
                            const PipePlan &plan, hipStream_t s);
 // Gram pass: per-chunk partials (and group sums, left in the slots of the

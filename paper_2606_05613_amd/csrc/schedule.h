@@ -43,11 +43,11 @@ __device__ __forceinline__ Sums block_scan(Sums s, Sums (&tot)[T / kWave]) {
 }
 
 // Checks the offsets and calls put(b, s) for b = 0 .. B with the sums over the
-// buckets before b (chunks of C elements, finalize groups by kSumDirect); false
+// buckets before b (chunks of C elements, no finalize groups below `direct`); false
 // (and no call) if the offsets are not 0 = o_0 <= ... <= o_B = N.
 template <int T, typename Put>
 __device__ __forceinline__ bool block_schedule(const int64_t *__restrict__ offs, int B, int64_t N, int64_t C,
-                                               Put put) {
+                                               int64_t direct, Put put) {
   __shared__ Sums tot[T / kWave];
   const int tid = threadIdx.x;
   int bad = offs[0] != 0 || offs[B] != N;
@@ -58,7 +58,7 @@ __device__ __forceinline__ bool block_schedule(const int64_t *__restrict__ offs,
     const int b = base + tid;
     const int64_t n = b < B ? offs[b + 1] - offs[b] : 0;
     const int64_t cnt = (n + C - 1) / C;
-    const int64_t groups = cnt < kSumDirect ? 0 : (cnt + kFinalizeGroup - 1) / kFinalizeGroup;
+    const int64_t groups = cnt < direct ? 0 : (cnt + kFinalizeGroup - 1) / kFinalizeGroup;
     const bool half = n > 0 && n - (cnt - 1) * C <= C / kCombineParts;
     const Sums own{cnt, (groups << 32) + (half ? 1 : 0)};
     const Sums s = block_scan<T>(own, tot);
@@ -98,10 +98,10 @@ struct ScheduleOut {
   uint32_t *err;
 };
 template <bool PARTS>
-__device__ __forceinline__ bool own_schedule(const int64_t *__restrict__ offs, int B, int64_t C, const ScheduleOut &o,
-                                             int64_t (&lcs)[kSelfBuckets + 1]) {
+__device__ __forceinline__ bool own_schedule(const int64_t *__restrict__ offs, int B, int64_t C, int64_t direct,
+                                             const ScheduleOut &o, int64_t (&lcs)[kSelfBuckets + 1]) {
   const bool writes = blockIdx.x == 0;
-  const bool ok = block_schedule<kThreads>(offs, B, o.N, C, [&](int b, Sums before) {
+  const bool ok = block_schedule<kThreads>(offs, B, o.N, C, direct, [&](int b, Sums before) {
     lcs[b] = PARTS ? before.parts() : before.chunks();
     if (writes) {
       o.cs[b] = before.chunks();

@@ -11,7 +11,7 @@ constexpr int kSchedThreads = 1024;
 
 // Workgroup 0.  chunk_start[b] = sum_{b' < b} ceil(n_b' / C) and, when
 // group_start is given, group_start[b] = the finalize groups of the buckets
-// before b (none in a bucket of fewer than kSumDirect chunks), part_start[b]
+// before b (none in a bucket of fewer than `direct` chunks), part_start[b]
 // their combine parts.
 // On invalid offsets every entry is 0 (so no chunk is processed) and the
 // error word gets kErrOffsets.  Otherwise the error word is cleared.  With a
@@ -19,7 +19,7 @@ constexpr int kSchedThreads = 1024;
 // kernel runs its tiled form (see PipePlan).  The other workgroups zero
 // `nsync` words at `sync`.
 __global__ __launch_bounds__(kSchedThreads) void schedule_kernel(
-    const int64_t *__restrict__ offs, int B, int64_t N, int64_t C, int64_t *__restrict__ cs,
+    const int64_t *__restrict__ offs, int B, int64_t N, int64_t C, int64_t direct, int64_t *__restrict__ cs,
     int64_t *__restrict__ gs, int64_t *__restrict__ ps, uint32_t *__restrict__ err, uint32_t *__restrict__ sync,
     int64_t nsync, PipePlan plan) {
   const int tid = threadIdx.x;
@@ -30,7 +30,7 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_kernel(
   }
   __shared__ unsigned long long load[kMaxPlanGroups];  // estimated ns of each group's buckets
   if (tid < kMaxPlanGroups) load[tid] = 0;
-  const bool ok = block_schedule<kSchedThreads>(offs, B, N, C, [&](int b, Sums before) {
+  const bool ok = block_schedule<kSchedThreads>(offs, B, N, C, direct, [&](int b, Sums before) {
     cs[b] = before.chunks();
     if (gs) gs[b] = before.groups();
     if (ps) ps[b] = before.parts();
@@ -52,13 +52,13 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_kernel(
 
 }  // namespace
 
-hipError_t launch_schedule(const int64_t *offsets, int B, int64_t N, int64_t C, int64_t *chunk_start,
+hipError_t launch_schedule(const int64_t *offsets, int B, int64_t N, int64_t C, int64_t direct, int64_t *chunk_start,
                            int64_t *group_start, int64_t *part_start, uint32_t *err, uint32_t *sync, int64_t nsync,
                            const PipePlan &plan, hipStream_t s) {
   // workgroup 0 schedules, up to 64 others clear
   const int64_t clear = (nsync + kSchedThreads - 1) / kSchedThreads;
   hipLaunchKernelGGL(schedule_kernel, dim3((unsigned)(1 + (clear < 64 ? clear : 64))), dim3(kSchedThreads), 0, s,
-                     offsets, B, N, C, chunk_start, group_start, part_start, err, sync,
+                     offsets, B, N, C, direct, chunk_start, group_start, part_start, err, sync,
                      nsync, plan);
   return hipGetLastError();
 }

@@ -1,5 +1,5 @@
 """The Gram finalize at the line where chunk slots are first added in groups
-(512 chunks in a bucket), the resolve call's finalize that also solves, and the
+(512 chunks in a bucket, fewer with many tasks), the resolve call's finalize that also solves, and the
 schedule that a streaming pass makes for itself, against float64 sums of the
 same bytes."""
 
@@ -27,10 +27,11 @@ def _gram64(x, offs):
 @pytest.mark.parametrize("K,dtype", [(2, "f32"), (16, "bf16")])
 def test_grouped_and_direct_sums(gpu_lib, K, dtype, past):
     """Buckets of no, one, 63 to 65 chunks, one a chunk and an element long, and
-    one of just below, at and just above 512 chunks, whose slots are first added
-    in groups from there on."""
+    one of just below, at and just above the line from which a bucket's slots are
+    first added in groups (64 for each thread of a pair: 512 chunks at most, with
+    16 tasks 192)."""
     C = CHUNK[K, dtype]
-    lens = [1, 0, 63 * C, 64 * C, 64 * C + 1, C + 1, 0, 20 * C - 2, (512 + past) * C - 2]
+    lens = [1, 0, 63 * C, 64 * C, 64 * C + 1, C + 1, 0, 20 * C - 2, ({2: 512, 16: 192}[K] + past) * C - 2, 513 * C]
     offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
     print(f"case finalize K={K} {dtype} N={offs[-1]}", flush=True)
     gen = torch.Generator(device="cuda")
